@@ -112,6 +112,10 @@ hipError_t launch_feature_layout_packed(int N, int d, int C, const float* x, voi
 // the edge pass; parts = 1: bf16.
 hipError_t launch_direct_layout(int N, int d, int C, int Cp, const void* x, bool x_is_f32, int parts, void* xd,
                                 float* row_scale, bool perm_channels, hipStream_t s);
+// The partial rows of segments that span ranges added in range order onto
+// their output rows, and the zero rows of segments without edges (the last
+// step of every range-split edge pass: a.n_range ranges, a.partial).
+hipError_t launch_range_fixup(const EdgeArgs& a, hipStream_t s);
 // parts = 2: fp32 features (fp16 two-part split), parts = 1: bf16 features
 hipError_t launch_cp_edge(const EdgeArgs& a, hipStream_t s);
 // Measurement ablation of the segmented sum (fp32 features, 2 <= L <= 4): the
