@@ -92,7 +92,8 @@ def forward_flops(N, E, d, C, R):
 
 def kernel_source_hash():
     h = hashlib.sha256()
-    for f in ("cp_edge_impl.hpp", "cp_edge.hip", "sh_device.hpp", "common.hpp"):
+    for f in ("cp_edge_impl.hpp", "cp_edge.hip", "cp_edge_mat_impl.hpp", "cp_edge_mat.hip", "sh_device.hpp",
+              "common.hpp"):
         h.update(open(os.path.join(ROOT, "paper_2507_01131_amd", "csrc", f), "rb").read())
     return h.hexdigest()[:16]
 
@@ -410,11 +411,15 @@ def main():
         "forward_tflops": forward_flops(N, E, d, C, R) / (ms_step * 1e-3) / 1e12,
     }
     if not bf16:
-        # fp16 MFMA work issued by the edge contraction: per edge, 32-channel
-        # tile and 32-rank tile, the packed K-reduction of the three part
-        # products, ceil(3 ceil(d/2) / 8) steps of 2*32*32*16 flops
-        pk_blocks = (3 * ((d + 1) // 2) + 7) // 8
-        executed = E * ((C + 31) // 32) * ((R + 31) // 32) * pk_blocks * 2 * 32 * 32 * 16
+        # fp16 MFMA work issued by the edge contraction, in 32x32x16 products:
+        # through per-edge matrices (degree 4, 97 to 128 ranks, at the size of
+        # a batch) three per 16 ranks and six per 32 channels an edge; else per
+        # edge, 32-channel tile and 32-rank tile the packed K-reduction of the
+        # three part products, ceil(3 ceil(d/2) / 8) steps
+        ct, rt = (C + 31) // 32, (R + 31) // 32
+        matrices = d == 25 and 96 < R <= 128 and C > 32 and E >= 50000
+        products = 6 * rt + 6 * ct if matrices else ct * rt * ((3 * ((d + 1) // 2) + 7) // 8)
+        executed = E * products * 2 * 32 * 32 * 16
         # the same algorithmic rate against the fp32 MFMA peak (can pass 1,
         # since the work runs on fp16 MFMA) and against the ceiling of fp32
         # products emulated by three fp16 products (fp16 peak / 3)
@@ -422,8 +427,8 @@ def main():
         line["roofline"]["emulated_fp32_ceiling"] = PEAK_FP16_MFMA_TFLOPS / 3
         line["roofline"]["frac_of_emulated_fp32_ceiling"] = achieved / (PEAK_FP16_MFMA_TFLOPS / 3)
         line["roofline"]["executed"] = {
-            "mfma": "v_mfma_f32_32x32x16_f16, three products of two-part fp16 splits per fp32 product, packed "
-                    "into one K-reduction",
+            "mfma": "v_mfma_f32_32x32x16_f16, three products of two-part fp16 splits per fp32 product, "
+                    + ("per-edge matrices" if matrices else "packed into one K-reduction"),
             "flops_per_launch": executed, "achieved": executed / (edge_ms * 1e-3) / 1e12,
             "peak": PEAK_FP16_MFMA_TFLOPS, "frac": executed / (edge_ms * 1e-3) / 1e12 / PEAK_FP16_MFMA_TFLOPS}
     if not bf16 and not args.no_comparator:

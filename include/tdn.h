@@ -206,11 +206,14 @@ tdn_status tdn_attention_forward(const tdn_problem* p, int32_t n_heads, int32_t 
  * with one choice of the edge pass replaced (the paper attributes its speed
  * to this kind of kernel-level choice, Sec. 3.2 "coalesced memory access"):
  *   TDN_ABL_FACTORS_GLOBAL  the factor's packed operand blocks read in the
- *                           edge loop from a per-workgroup copy in global
- *                           memory instead of registers or LDS;
+ *                           edge loop from global memory (a copy per
+ *                           workgroup, or the launch's own where the forward
+ *                           goes through per-edge matrices) instead of
+ *                           registers or LDS;
  *   TDN_ABL_Y_TABLE         the edge harmonics precomputed into a workspace
  *                           table by a kernel of their own and read by the
- *                           edge kernel instead of evaluated in it;
+ *                           edge kernel instead of evaluated in it (in the
+ *                           rank form at every size);
  *   TDN_ABL_VALU            the contraction, the segment sum and D in fp32
  *                           fused multiply-adds on the vector ALUs (one
  *                           workgroup per destination) instead of fp16 MFMA

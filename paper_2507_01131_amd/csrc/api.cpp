@@ -303,9 +303,18 @@ tdn::EdgeArgs edge_args(const tdn_problem& p, const int32_t* offsets, const int3
   return a;
 }
 
+// Whether the edge passes of this problem go through per-edge matrices.
+bool use_mat(const tdn_problem& p) {
+  const bool bf16 = p.feat_dtype == TDN_BF16;
+  return tdn::mat_use(p.L, p.R, p.C, bf16, tdn::edge_plan(p.L, p.R, p.C, p.n_radial, bf16, p.n_edges).n_range);
+}
+
 // Features of the CP edge pass: the packed fp16 split of fp32 features, or
 // the bf16 operand blocks (bf16 problems; an fp32 input is rounded).
-hipError_t edge_features(const tdn_problem& p, const void* x, bool x_is_f32, void* xt, hipStream_t s) {
+hipError_t edge_features(const tdn_problem& p, const void* x, bool x_is_f32, bool mat, void* xt, hipStream_t s) {
+  if (mat)
+    return tdn::launch_feature_layout_mat(p.n_nodes, p.C, x, x_is_f32, feature_parts(p), xt,
+                                          feature_parts(p) == 2 ? row_scales(p, xt) : nullptr, s);
   if (feature_parts(p) == 2)
     return tdn::launch_feature_layout_packed(p.n_nodes, dim_of(p.L), p.C, static_cast<const float*>(x), xt,
                                              row_scales(p, xt), s);
@@ -324,7 +333,8 @@ hipError_t edge_pass_ranks(const tdn_problem& p, const int32_t* offsets, const i
   const int nch = rank_chunks(p.R);
   if (nch == 1) {
     const tdn::EdgeArgs a = edge_args(p, offsets, perm, gather, key, edge_vec, KF, EF, B, radial_w, feat, out, partial);
-    return atomic ? tdn::launch_cp_edge_atomic(a, s) : tdn::launch_cp_edge(a, s);
+    return atomic ? tdn::launch_cp_edge_atomic(a, s)
+                  : (use_mat(p) ? tdn::launch_cp_edge_mat(a, s) : tdn::launch_cp_edge(a, s));
   }
   if (atomic) return hipErrorInvalidValue;
   const int d = dim_of(p.L);
@@ -357,7 +367,7 @@ hipError_t forward_edge_pass(const tdn_problem& p, const int32_t* offsets, const
                              float* ztmp, hipStream_t s, bool atomic = false) {
   {
     Timed t("feature_layout", s);
-    hipError_t e = edge_features(p, x, p.feat_dtype == TDN_F32, xt, s);
+    hipError_t e = edge_features(p, x, p.feat_dtype == TDN_F32, !atomic && use_mat(p), xt, s);
     if (e != hipSuccess) return e;
   }
   Timed t(atomic ? "cp_edge_fwd_atomic" : "cp_edge_fwd", s);
@@ -525,9 +535,11 @@ tdn_status tdn_ablation_forward(const tdn_problem* p, int32_t variant, const voi
   float* Z = z_save ? z_save : reinterpret_cast<float*>(ws + lay.z);
   float* partial = reinterpret_cast<float*>(ws + lay.part);
   tdn::EdgeArgs a = edge_args(*p, offsets, perm, src, dst, edge_vec, A, D, B, radial_w, ws + lay.xt, Z, partial);
+  // (the table's variant keeps the rank form at every size)
+  const bool mat = variant == tdn::kAblFactorsGlobal && use_mat(*p);
   if (variant != tdn::kAblValu) {
     Timed t("feature_layout", stream);
-    TDN_HIP(edge_features(*p, x, true, ws + lay.xt, stream));
+    TDN_HIP(edge_features(*p, x, true, mat, ws + lay.xt, stream));
   }
   if (variant == tdn::kAblFactorsGlobal) a.fa_global = ws + lay.total;
   if (variant == tdn::kAblYTable && E > 0) {
@@ -538,7 +550,8 @@ tdn_status tdn_ablation_forward(const tdn_problem* p, int32_t variant, const voi
   }
   {
     Timed t("cp_edge_fwd_ablation", stream);
-    TDN_HIP(tdn::launch_cp_edge_ablation(a, variant, static_cast<const float*>(x), stream));
+    TDN_HIP(mat ? tdn::launch_cp_edge_mat(a, stream)
+                : tdn::launch_cp_edge_ablation(a, variant, static_cast<const float*>(x), stream));
   }
   {
     Timed t("node_gemm", stream);
@@ -614,7 +627,7 @@ tdn_status tdn_attention_forward(const tdn_problem* p, int32_t n_heads, int32_t 
   float* Z = z_save ? z_save : reinterpret_cast<float*>(ws + lay.z);
   {
     Timed t("feature_layout", stream);
-    TDN_HIP(edge_features(*p, x, true, ws + lay.xt, stream));
+    TDN_HIP(edge_features(*p, x, true, use_mat(*p), ws + lay.xt, stream));
   }
   {
     Timed t("cp_edge_fwd_att", stream);
@@ -622,7 +635,7 @@ tdn_status tdn_attention_forward(const tdn_problem* p, int32_t n_heads, int32_t 
                                 reinterpret_cast<float*>(ws + lay.part));
     a.alpha = al_sorted;
     a.n_heads = H;
-    TDN_HIP(tdn::launch_cp_edge_att(a, stream));
+    TDN_HIP(use_mat(*p) ? tdn::launch_cp_edge_mat(a, stream) : tdn::launch_cp_edge_att(a, stream));
   }
   {
     Timed t("node_gemm", stream);
@@ -666,7 +679,7 @@ tdn_status tdn_cp_tp3_forward(const tdn_problem* p, const void* x, const float* 
   void* xt = ws + lay.xt;
   {
     Timed t("feature_layout", stream);
-    TDN_HIP(edge_features(*p, x, true, xt, stream));
+    TDN_HIP(edge_features(*p, x, true, false, xt, stream));
   }
   {
     Timed t("cp_edge_fwd_t3", stream);
@@ -1037,7 +1050,7 @@ tdn_status tdn_cp_tp_backward(const tdn_problem* p, const void* x, const float* 
     // bf16); fp32 problems on the fp16 two-part split of Gz
     {
       Timed t("feature_layout", stream);
-      TDN_HIP(edge_features(*p, Gz, true, ws + lay.xt, stream));
+      TDN_HIP(edge_features(*p, Gz, true, use_mat(*p), ws + lay.xt, stream));
     }
     Timed t("cp_edge_bwd_src", stream);
     TDN_HIP(edge_pass_ranks(*p, off_src, perm_src, dst, src, edge_vec, D, A, B, radial_w, ws + lay.xt, grad_x,

@@ -214,6 +214,76 @@ hipError_t launch_packed_pn(int N, int d, int C, const float* x, uint32_t* xp, f
   return hipGetLastError();
 }
 
+// The same for the L = 4 pass through per-edge matrices
+// (launch_feature_layout_mat): lane (h, c) holds the rows acc_krow(q, h, j),
+// P = 2 fp16 parts with the node's scale, P = 1 bf16.
+template <int MT, int P, typename TI>
+__global__ __launch_bounds__(256) void k_feature_layout_mat(int C, const TI* __restrict__ x, uint32_t* __restrict__ xp,
+                                                            float* __restrict__ row_scale) {
+  constexpr int d = 25;
+  __shared__ float red[4];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int h = lane >> 5, l32 = lane & 31;
+  const int n_ct = (C + 31) / 32;
+  const int node = blockIdx.x;
+  float v[MT][14];
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const int c = (wave + 4 * m) * 32 + l32;
+    const TI* src = x + size_t(node) * d * C + c;
+#pragma unroll
+    for (int r = 0; r < 14; ++r) {
+      const int row = r < 8 ? acc_krow(0, h, r) : acc_krow(1, h, r - 8);
+      v[m][r] = (c < C && row < d) ? to_f32(src[size_t(row) * C]) : 0.f;
+    }
+  }
+  float sc = 1.f;
+  if constexpr (P == 2) {
+    float mx = 0.f;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int r = 0; r < 14; ++r) mx = fmaxf(mx, fabsf(v[m][r]));
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+    if (lane == 0) red[wave] = mx;
+    __syncthreads();
+    mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    const int e = f16_split_exponent(mx);
+    sc = ldexpf(1.f, -e);
+    if (tid == 0) row_scale[node] = ldexpf(1.f, e);
+  }
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    const int ct = wave + 4 * m;
+    if (ct >= n_ct) break;
+    uint32_t w[P][7];
+#pragma unroll
+    for (int j = 0; j < 7; ++j) {
+      if constexpr (P == 2)
+        split_f16x2_pair(v[m][2 * j] * sc, v[m][2 * j + 1] * sc, w[0][j], w[P - 1][j]);
+      else
+        w[0][j] = pack_bf16x2_rne(v[m][2 * j], v[m][2 * j + 1]);
+    }
+    uint32_t* o = xp + (size_t(node) * n_ct + ct) * 64 * 7 * P;
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+      *reinterpret_cast<u32x4*>(o + (p * 64 + lane) * 4) = u32x4{w[p][0], w[p][1], w[p][2], w[p][3]};
+#pragma unroll
+      for (int t = 0; t < 3; ++t) o[P * 256 + (p * 64 + lane) * 3 + t] = w[p][4 + t];
+    }
+  }
+}
+
+template <int P, typename TI>
+hipError_t launch_mat_layout(int N, int C, const TI* x, uint32_t* w, float* row_scale, hipStream_t s) {
+  if (C <= 128)
+    k_feature_layout_mat<1, P, TI><<<dim3(N), dim3(256), 0, s>>>(C, x, w, row_scale);
+  else
+    k_feature_layout_mat<2, P, TI><<<dim3(N), dim3(256), 0, s>>>(C, x, w, row_scale);
+  return hipGetLastError();
+}
+
 template <int DP, int P, typename TI>
 hipError_t launch_dp(int N, int d, int C, const TI* x, uint16_t* xs, float* row_scale, hipStream_t s) {
   const size_t lds = (size_t(d) * C + 4) * 4;
@@ -334,6 +404,19 @@ hipError_t launch_feature_layout_packed(int N, int d, int C, const float* x, voi
     case 25: return launch_packed_pn<25>(N, d, C, x, w, row_scale, s);
     default: return hipErrorInvalidValue;
   }
+}
+
+hipError_t launch_feature_layout_mat(int N, int C, const void* x, bool x_is_f32, int parts, void* xp,
+                                     float* row_scale, hipStream_t s) {
+  if (N == 0) return hipSuccess;
+  if (!x || !xp || C < 1 || C > 256 || (parts != 1 && parts != 2)) return hipErrorInvalidValue;
+  uint32_t* w = static_cast<uint32_t*>(xp);
+  if (parts == 2) {
+    if (!x_is_f32 || !row_scale) return hipErrorInvalidValue;
+    return launch_mat_layout<2>(N, C, static_cast<const float*>(x), w, row_scale, s);
+  }
+  return x_is_f32 ? launch_mat_layout<1>(N, C, static_cast<const float*>(x), w, nullptr, s)
+                  : launch_mat_layout<1>(N, C, static_cast<const uint16_t*>(x), w, nullptr, s);
 }
 
 hipError_t launch_feature_layout(int N, int d, int C, const void* x, bool x_is_f32, int parts, void* xs,

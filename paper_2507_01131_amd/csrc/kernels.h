@@ -65,6 +65,7 @@ struct EdgeArgs {
   int n_heads;
   // measurement ablations only (launch_cp_edge_ablation):
   void* fa_global;           // factors from global memory: per workgroup a copy of its packed factor blocks
+                             // (the per-edge matrices' pass: not NULL, its operands are read where they lie)
   const float* y_table;      // harmonics table: [E, d] Y of each edge by edge id (launch_sh)
 };
 // Edge ranges of the pass for this problem on the current device:
@@ -112,6 +113,20 @@ hipError_t launch_feature_layout_packed(int N, int d, int C, const float* x, voi
 // the edge pass; parts = 1: bf16.
 hipError_t launch_direct_layout(int N, int d, int C, int Cp, const void* x, bool x_is_f32, int parts, void* xd,
                                 float* row_scale, bool perm_channels, hipStream_t s);
+// The L = 4 pass through per-edge matrices (cp_edge_mat_impl.hpp): the same
+// result as launch_cp_edge (or, with a.alpha, launch_cp_edge_att) with feat in
+// launch_feature_layout_mat's words; a.pieces_per_block is not used.
+// n_range: the plan's.
+bool mat_use(int L, int R, int C, bool bf16, int n_range);
+hipError_t launch_cp_edge_mat(const EdgeArgs& a, hipStream_t s);
+// Its features (d = 25): lane (h, c) of channel tile ct holds the degree rows
+// acc_krow(q, h, j): q = 0, j = 0..7 in four words of fp16 hi parts, then four
+// of lo parts, and q = 1, j = 0..5 in three words each (rows from 26 on do not
+// exist); per node and tile [part][64 lanes][4] words, then [part][64
+// lanes][3].  parts = 1: bf16, one part.  row_scale as
+// launch_feature_layout_packed (parts = 2).
+hipError_t launch_feature_layout_mat(int N, int C, const void* x, bool x_is_f32, int parts, void* xp,
+                                     float* row_scale, hipStream_t s);
 // The partial rows of segments that span ranges added in range order onto
 // their output rows, and the zero rows of segments without edges (the last
 // step of every range-split edge pass: a.n_range ranges, a.partial).

@@ -1,0 +1,104 @@
+"""GPU parity of the degree-4 edge pass through per-edge matrices at the edges
+of its tiles, against the oracle on sampled nodes (a hub whose segment spans
+many ranges and nodes without edges among them).  The pass is taken from a
+range per team of the device on, so the graphs have 50 to 70 thousand edges.
+Ranks just past a 32-rank tile and at the last one, channel counts with a part
+tile, two, three, five and eight tiles, two and sixteen radial functions, odd
+range lengths, both feature types, rows over 40 binary orders, forward,
+backward and attention.  The bounds are those of every other parity test: 1e-5
+for fp32 problems (the two-part fp16 splits keep 22 bits, the sums are fp32),
+2e-2 for bf16 ones (8 bits, rounded features and matrices)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2507_01131_amd as tdn
+import workloads
+from oracle import attention, layer
+from tests._gpu_helpers import (check_rows, check_scaled, device_inputs, grad_vec_scale, random_factors, rel_err,
+                                tol)
+
+pytestmark = pytest.mark.gpu
+
+HUB = 7  # (no node from N - 5 on has edges)
+
+
+def _t(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def _problem(seed, N, E, C, R, n_radial, srt, dtype, wide=False):
+    w = workloads.random_graph(seed, n_nodes=N, n_edges=E, L=4, C=C, R=R, feat_dtype=dtype)
+    rng = np.random.default_rng(seed)
+    w["n_radial"] = n_radial
+    w["radial_w"] = (rng.standard_normal((n_radial, R)) / np.sqrt(n_radial)).astype(np.float32)
+    ei = np.minimum(w["edge_index"], N - 6)
+    ei[1, 1000:1400] = HUB
+    ei[0, 2000:2500] = HUB
+    if srt:
+        o = np.argsort(ei[1], kind="stable")
+        ei, w["edge_vec"], w["presorted"] = ei[:, o], w["edge_vec"][o], True
+    w["edge_index"] = np.ascontiguousarray(ei)
+    if wide:
+        w["x"] = np.ldexp(w["x"], rng.integers(-20, 21, (N, 1, 1))).astype(np.float32)
+        w["grad_out"] = np.ldexp(w["grad_out"], rng.integers(-20, 21, (N, 1, 1))).astype(np.float32)
+    return w, random_factors(4, R, seed)
+
+
+def _nodes(N, seed):
+    return np.unique(np.concatenate([[0, HUB, N - 6, N - 1], np.random.default_rng(seed).integers(0, N, 12)]))
+
+
+CASES = [
+    # N, E, C, R, n_radial, sorted, dtype, wide
+    (1500, 60001, 80, 65, 2, False, "f32", False), (1500, 60010, 96, 96, 16, True, "f32", False),
+    (1500, 50023, 48, 97, 8, False, "f32", False), (1500, 50001, 128, 128, 9, False, "f32", True),
+    (700, 60007, 160, 127, 8, False, "f32", False), (500, 50001, 256, 66, 8, True, "f32", False),
+    (1500, 60003, 32, 128, 8, False, "bf16", False), (1500, 70001, 128, 97, 3, True, "bf16", False),
+    (500, 60005, 144, 70, 8, False, "bf16", False), (500, 60001, 256, 128, 8, False, "bf16", False),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"E{c[1]}C{c[2]}R{c[3]}q{c[4]}{c[6]}")
+def test_forward_and_backward(case):
+    w, (A, B, D) = _problem(900 + case[2], *case)
+    inp = device_inputs(w, A, B, D)
+    res = tdn.forward(inp["x"], inp["edge_vec"], inp["edge_index"], inp["A"], inp["B"], inp["D"], inp["W"],
+                      inp["radial_w"], L=4, r_cut=w["r_cut"], edges_sorted=w["presorted"])
+    gx, _, gv = tdn.backward(res, _t(w["grad_out"]))
+    torch.cuda.synchronize()
+    args = (w["x"], w["edge_index"], w["edge_vec"], A, B, D, w["W"], w["radial_w"], w["r_cut"], 4)
+    t = tol(w)
+    nodes = _nodes(w["N"], 1)
+    ref = layer.forward_at_nodes(nodes, *args)
+    out = res.out.cpu().numpy()
+    assert rel_err(out[nodes], ref) < t
+    check_rows(out[nodes], ref, t, "out")
+    assert not out[w["N"] - 1].any()
+    sel = np.nonzero(np.isin(w["edge_index"][0], nodes))[0]
+    rx, _, rv = layer.backward(*args, w["grad_out"], perm=sel)
+    assert rel_err(gx.cpu().numpy()[nodes], rx[nodes]) < t
+    check_rows(gx.cpu().numpy()[nodes], rx[nodes], t, "grad_x")
+    check_scaled(gv.cpu().numpy()[sel], rv[sel], grad_vec_scale(w, A, B, D, edges=sel), t, "grad_edge_vec")
+    assert np.all(np.isfinite(out)) and bool(torch.isfinite(gx).all())
+
+
+@pytest.mark.parametrize("N,E,C,R,H", [(1500, 60003, 96, 65, 3), (1500, 50001, 128, 128, 4), (500, 60002, 256, 97, 8)])
+def test_attention(N, E, C, R, H):
+    w, (A, B, D) = _problem(950 + C, N, E, C, R, 8, False, "f32")
+    rng = np.random.default_rng(E)
+    W1 = (2 * rng.standard_normal((2 * C + 8, 16)) / np.sqrt(2 * C + 8)).astype(np.float32)
+    w2 = (rng.standard_normal((16, H)) / 2).astype(np.float32)
+    res, _ = tdn.attention_forward(_t(w["x"]), _t(w["edge_vec"]), _t(w["edge_index"]), _t(A), _t(B), _t(D),
+                                   _t(w["W"]), _t(w["radial_w"]), _t(W1), _t(w2), L=4, r_cut=w["r_cut"],
+                                   edges_sorted=False)
+    torch.cuda.synchronize()
+    nodes = _nodes(N, 2)
+    perm, _ = layer.stable_sort_by_key(w["edge_index"][1], N)
+    sub = perm[np.isin(w["edge_index"][1][perm], nodes)]
+    ref, _ = attention.forward(w["x"], w["edge_index"], w["edge_vec"], A, B, D, w["W"], w["radial_w"], W1, w2,
+                               w["r_cut"], 4, perm=sub)
+    out = res.out.cpu().numpy()
+    assert np.all(np.isfinite(out))
+    assert rel_err(out[nodes], ref[nodes]) < tol(w)
+    check_rows(out[nodes], ref[nodes], tol(w), "out")
