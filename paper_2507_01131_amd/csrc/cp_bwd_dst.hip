@@ -2,13 +2,15 @@
 // kernel on bf16 MFMA (cp_bwd_dst2_l<L>.hip), else, or where its LDS layout
 // does not fit, the per-segment kernels: the factored form for d <= 32
 // (cp_bwd_sg_<dtype>.hip), the direct form on the k-tile count 2 for d <= 64
-// (cp_bwd_dst_m2_<dtype>.hip); each in its own translation unit.
+// (cp_bwd_dst_m2_<dtype>.hip, then cp_bwd_edge.hip); each in its own
+// translation unit.
 #include "cp_bwd_dst2_impl.hpp"
 
 namespace tdn {
 namespace bwd_detail {
 template <int MT, bool BF>
 hipError_t launch_mt(const BwdDstArgs& a, hipStream_t s);
+hipError_t launch_edge(const BwdDstArgs& a, hipStream_t s);
 }
 namespace bwd_sg_detail {
 template <bool BF16>
@@ -75,8 +77,9 @@ hipError_t launch_bwd_dst(const BwdDstArgs& a, bool x_bf16, hipStream_t s) {
   }
   if (a.d <= 32)
     return x_bf16 ? bwd_sg_detail::launch_sg_any<true>(a, s) : bwd_sg_detail::launch_sg_any<false>(a, s);
-  if (!a.xc || (!x_bf16 && !a.x_scale)) return hipErrorInvalidValue;
-  return x_bf16 ? bwd_detail::launch_mt<2, true>(a, s) : bwd_detail::launch_mt<2, false>(a, s);
+  if (!a.xc || (!x_bf16 && !a.x_scale) || !a.dg) return hipErrorInvalidValue;
+  const hipError_t e = x_bf16 ? bwd_detail::launch_mt<2, true>(a, s) : bwd_detail::launch_mt<2, false>(a, s);
+  return e != hipSuccess ? e : bwd_detail::launch_edge(a, s);
 }
 
 }  // namespace tdn

@@ -111,13 +111,6 @@ __host__ __device__ constexpr MatSmem mat_smem(int RS, bool bf) {
   return s;
 }
 
-// LDS accesses before the barrier are done before any after it; global loads
-// stay in flight across it.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-}
 __device__ constexpr float kRecip[5] = {1.f, 1.f / 2.f, 1.f / 3.f, 1.f / 4.f, 1.f / 5.f};
 // Order m (and -m) of the harmonics of a unit vector, l = m .. 4.
 __device__ __forceinline__ void sh_column(int m, float x, float y, float z, float* Y) {

@@ -284,14 +284,14 @@ struct BwdDstArgs {
   int n_range;              // equal edge ranges (bwd_dst_plan)
   int pieces_per_block;     // ranges per workgroup
   float* drho;              // [E, R] by edge id: dL/drho_e, or nullptr (not stored); per-segment kernels
-  float* bt;                // direct kernel (d > 32): workspace of (d + n_radial) R floats for B^T
-                            // [R, d] and Wrad^T [R, n_radial], written by its launch
+                            // and the direct form (d > 32)
   // range kernel only:
   float* wrad_part;         // [n_range / pieces_per_block, n_radial, R]: each workgroup's share of
                             // grad_radial_w (sum them in order), or nullptr
   const void* gzc;          // Gz in the layout of xc (launch_direct_layout): selects the split form
   const float* gz_scale;    // fp32 problems: row_scale of that layout
-  float* dg;                // split form: [E, R] dL/dg by sorted edge position (written, then read)
+  float* dg;                // split form: [E, R] dL/dg by sorted edge position (written, then read);
+                            // direct form: by edge id, may be drho
 };
 // Edge ranges of the destination-side kernel on the current device
 // (n_range = 0 when the problem takes the per-segment kernels: d > 32 or no

@@ -1,0 +1,44 @@
+"""GPU parity of the backward's destination side at d > 32 (the contraction
+over channels and the per-edge kernel after it) at the edges of its tiles,
+against the oracle: one to eight 32-rank tiles, odd counts among them, two,
+four and eight channel tiles, one edge short of and past a chunk of 32 and a
+block of 64, a segment of several blocks, nodes without edges, both feature
+types.  The bounds are those of every other parity test (1e-5 for fp32
+problems, 2e-2 for bf16 ones)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2507_01131_amd as tdn
+import workloads
+from oracle import layer
+from tests._gpu_helpers import (check_elementwise, check_scaled, device_inputs, grad_vec_scale, random_factors,
+                                rel_err, tol)
+
+pytestmark = pytest.mark.gpu
+
+# L, C, R, N, E, edges into one node, dtype
+CASES = [(5, 32, 17, 40, 31, 0, "f32"), (6, 64, 96, 9, 33, 33, "f32"), (5, 128, 161, 300, 64, 3, "f32"),
+         (6, 96, 225, 30, 390, 193, "f32"), (5, 256, 256, 12, 97, 65, "f32"), (6, 48, 160, 20, 161, 129, "bf16"),
+         (5, 128, 224, 25, 700, 0, "bf16")]
+
+
+@pytest.mark.parametrize("L,C,R,N,E,hub,dtype", CASES)
+def test_edge_and_radial_gradients(L, C, R, N, E, hub, dtype):
+    w = workloads.random_graph(800 + E, n_nodes=N, n_edges=E, L=L, C=C, R=R, feat_dtype=dtype)
+    w["edge_index"][1, :hub] = 3
+    A, B, D = random_factors(L, R, E)
+    inp = device_inputs(w, A, B, D)
+    res = tdn.forward(inp["x"], inp["edge_vec"], inp["edge_index"], inp["A"], inp["B"], inp["D"], inp["W"],
+                      inp["radial_w"], L=L, r_cut=w["r_cut"], edges_sorted=False)
+    G = torch.from_numpy(w["grad_out"]).cuda()
+    _, _, gv, gr = tdn.backward(res, G, need_radial=True)
+    _, _, gv2 = tdn.backward(res, G)
+    torch.cuda.synchronize()
+    _, _, rv, rr = layer.backward(w["x"], w["edge_index"], w["edge_vec"], A, B, D, w["W"], w["radial_w"],
+                                  w["r_cut"], L, w["grad_out"], return_radial=True)
+    assert torch.equal(gv, gv2)  # with and without the radial-weight gradient
+    assert rel_err(gv.cpu(), rv) < tol(w)
+    check_scaled(gv.cpu(), rv, grad_vec_scale(w, A, B, D), tol(w), "grad_edge_vec")
+    assert rel_err(gr.cpu(), rr) < tol(w)
+    check_elementwise(gr.cpu(), rr, tol(w), "grad_radial_w")
