@@ -397,7 +397,8 @@ tdn_status tdn_spherical_harmonics(int32_t L, int32_t E, const float* edge_vec, 
  * ("cp_edge_fwd", "cp_edge_fwd_att", "attention_weights", "cp_edge_fwd_atomic", "cp_edge_fwd_ablation",
  * "sh_table", "cp_edge_fwd_t3",
  * "dense_edge_fwd", "dense_edge_unshared",
- * "path_gemm", "radius_graph", "feature_layout",
+ * "path_gemm", "radius_graph", "edge_factors" (the launch before the layout where an edge pass
+ * goes through per-edge matrices), "feature_layout",
  * "channel_layout", "cp_edge_bwd_src", "cp_bwd_dst", "radial_grad", "node_gemm", "gram",
  * "sort");
  * reset = 1 clears that kernel's record. */

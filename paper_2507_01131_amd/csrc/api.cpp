@@ -308,10 +308,20 @@ bool use_mat(const tdn_problem& p) {
 }
 
 // Features of the CP edge pass: the packed fp16 split of fp32 features, or
-// the bf16 operand blocks (bf16 problems; an fp32 input is rounded).
-hipError_t edge_features(const tdn_problem& p, const void* x, bool x_is_f32, bool mat, void* xt, hipStream_t s) {
+// the bf16 operand blocks (bf16 problems; an fp32 input is rounded).  Per-edge
+// matrices: the factors' operands (to ef_ops) come first, with the rows' scales.
+hipError_t edge_features(const tdn_problem& p, const void* x, bool x_is_f32, bool mat, const float* KF,
+                         const float* EF, const float* B, const float* radial_w, void* ef_ops, void* xt,
+                         hipStream_t s) {
+  if (mat) {
+    Timed t("edge_factors", s);
+    const hipError_t e = tdn::launch_mat_factor(p.R, p.n_radial, EF, KF, B, radial_w, ef_ops, s);
+    if (e != hipSuccess) return e;
+  }
+  Timed t("feature_layout", s);
   if (mat)
-    return tdn::launch_feature_layout_mat(p.n_nodes, p.C, x, x_is_f32, feature_parts(p), xt,
+    return tdn::launch_feature_layout_mat(p.n_nodes, p.C, x, x_is_f32, feature_parts(p),
+                                          tdn::mat_row_exp(p.R, ef_ops), xt,
                                           feature_parts(p) == 2 ? row_scales(p, xt) : nullptr, s);
   if (feature_parts(p) == 2)
     return tdn::launch_feature_layout_packed(p.n_nodes, dim_of(p.L), p.C, static_cast<const float*>(x), xt,
@@ -363,11 +373,9 @@ hipError_t forward_edge_pass(const tdn_problem& p, const int32_t* offsets, const
                              const int32_t* dst, const float* edge_vec, const float* A, const float* B, const float* D,
                              const float* radial_w, const void* x, void* xt, float* partial, float* Z, float* fsl,
                              float* ztmp, hipStream_t s, bool atomic = false) {
-  {
-    Timed t("feature_layout", s);
-    hipError_t e = edge_features(p, x, p.feat_dtype == TDN_F32, !atomic && use_mat(p), xt, s);
-    if (e != hipSuccess) return e;
-  }
+  const hipError_t e =
+      edge_features(p, x, p.feat_dtype == TDN_F32, !atomic && use_mat(p), A, D, B, radial_w, partial, xt, s);
+  if (e != hipSuccess) return e;
   Timed t(atomic ? "cp_edge_fwd_atomic" : "cp_edge_fwd", s);
   return edge_pass_ranks(p, offsets, perm, src, dst, edge_vec, A, D, B, radial_w, xt, Z, partial, fsl, ztmp, s,
                          atomic);
@@ -535,10 +543,8 @@ tdn_status tdn_ablation_forward(const tdn_problem* p, int32_t variant, const voi
   tdn::EdgeArgs a = edge_args(*p, offsets, perm, src, dst, edge_vec, A, D, B, radial_w, ws + lay.xt, Z, partial);
   // (the table's variant keeps the rank form at every size)
   const bool mat = variant == tdn::kAblFactorsGlobal && use_mat(*p);
-  if (variant != tdn::kAblValu) {
-    Timed t("feature_layout", stream);
-    TDN_HIP(edge_features(*p, x, true, mat, ws + lay.xt, stream));
-  }
+  if (variant != tdn::kAblValu) 
+    TDN_HIP(edge_features(*p, x, true, mat, A, D, B, radial_w, partial, ws + lay.xt, stream));
   if (variant == tdn::kAblFactorsGlobal) a.fa_global = ws + lay.total;
   if (variant == tdn::kAblYTable && E > 0) {
     float* yt = reinterpret_cast<float*>(ws + lay.total);
@@ -623,10 +629,7 @@ tdn_status tdn_attention_forward(const tdn_problem* p, int32_t n_heads, int32_t 
                                   edge_vec, Pt, Ps, att_w1, att_w2, al_sorted, alpha, stream));
   }
   float* Z = z_save ? z_save : reinterpret_cast<float*>(ws + lay.z);
-  {
-    Timed t("feature_layout", stream);
-    TDN_HIP(edge_features(*p, x, true, use_mat(*p), ws + lay.xt, stream));
-  }
+  TDN_HIP(edge_features(*p, x, true, use_mat(*p), A, D, B, radial_w, ws + lay.part, ws + lay.xt, stream));
   {
     Timed t("cp_edge_fwd_att", stream);
     tdn::EdgeArgs a = edge_args(*p, offsets, perm, src, dst, edge_vec, A, D, B, radial_w, ws + lay.xt, Z,
@@ -675,10 +678,7 @@ tdn_status tdn_cp_tp3_forward(const tdn_problem* p, const void* x, const float* 
   if (N == 0) return TDN_OK;
   float* Z = z_save ? z_save : reinterpret_cast<float*>(ws + lay.z);
   void* xt = ws + lay.xt;
-  {
-    Timed t("feature_layout", stream);
-    TDN_HIP(edge_features(*p, x, true, false, xt, stream));
-  }
+  TDN_HIP(edge_features(*p, x, true, false, A, D, B, radial_w, nullptr, xt, stream));
   {
     Timed t("cp_edge_fwd_t3", stream);
     tdn::EdgeArgs a = edge_args(*p, offsets, perm, src, dst, edge_vec, A, D, B, radial_w, xt, Z,
@@ -1046,10 +1046,7 @@ tdn_status tdn_cp_tp_backward(const tdn_problem* p, const void* x, const float* 
     }
     // bf16 problems run the grad_x pass on bf16 MFMA too (Gz rounded to
     // bf16); fp32 problems on the fp16 two-part split of Gz
-    {
-      Timed t("feature_layout", stream);
-      TDN_HIP(edge_features(*p, Gz, true, use_mat(*p), ws + lay.xt, stream));
-    }
+    TDN_HIP(edge_features(*p, Gz, true, use_mat(*p), D, A, B, radial_w, ws + lay.part, ws + lay.xt, stream));
     Timed t("cp_edge_bwd_src", stream);
     TDN_HIP(edge_pass_ranks(*p, off_src, perm_src, dst, src, edge_vec, D, A, B, radial_w, ws + lay.xt, grad_x,
                             reinterpret_cast<float*>(ws + lay.part), fsl, gtmp, stream));

@@ -23,106 +23,189 @@ TDN_MAT_RS(8)
 
 namespace {
 
-// The builder's factor operands, per rank step s of 16 and lane (h, l): EF
-// 2^-e_E, row l, ranks 16 s + 8 h + j in fp32 ([RS][2][64 lanes] x 16 bytes);
-// KF 2^-e_K, row l and the same ranks in two fp16 parts ([RS][2][64 lanes] x
-// 16 bytes); then MatConst.  Zero past d and R.  One wave per step, every
-// workgroup taking the factors' largest magnitudes itself; the last workgroup
-// writes MatConst.
-__global__ __launch_bounds__(256) void k_mat_factor(int R, int RS, int n_radial, const float* __restrict__ EF,
-                                                    const float* __restrict__ KF, const float* __restrict__ B,
-                                                    const float* __restrict__ Wrad, char* __restrict__ out) {
-  __shared__ float red[16];
+// Exponent of a magnitude as frexp gives it; kNone for 0, and for an infinity or
+// NaN (which stay in the operands and take no part in the scales).
+constexpr int kNone = -(1 << 20);
+__device__ __forceinline__ int mag_exp(float v) {
+  int e = kNone;
+  if (v != 0.f && fabsf(v) <= 3.4028234e38f) (void)frexpf(v, &e);
+  return e;
+}
+
+// The builder's factor operands, per rank step s of 16 and lane (h, l): EF,
+// row l, ranks 16 s + 8 h + j in fp32 ([RS][2][64 lanes] x 16 bytes); KF, row l
+// and the same ranks in two fp16 parts ([RS][2][64 lanes] x 16 bytes), both
+// scaled per row and then per column; zero past d and R (block 0).  Then the rest
+// of MatOps (block 1).  Both blocks find the scales, with exponents as integers.
+// Bound by the latency of its phases and, as a lone wave issues an instruction
+// every eight cycles, by how many waves share them: 7 us; 12.5 with four waves a
+// block and 15 with a step's operands per wave and the norms a row per wave (8.8
+// with one scale per factor, in the latter form).
+__global__ __launch_bounds__(1024) void k_mat_factor(int R, int RS, int n_radial, const float* __restrict__ EF,
+                                                     const float* __restrict__ KF, const float* __restrict__ B,
+                                                     const float* __restrict__ Wrad, char* __restrict__ out) {
+  constexpr int kMost = 128, kParts = 8, kRowsPer = (kD + kParts - 1) / kParts;
+  __shared__ float sF[2][kD][kMost + 1], sPart[kParts][kMost];
+  __shared__ int sG[2][kMost], sCol[3][kMost], sRow[2][kTile], sTop[3], sMax[18];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  float mE = 0.f, mK = 0.f;
-#pragma unroll 4
-  for (int i = tid; i < kD * R; i += 256) {
-    mE = fmaxf(mE, fabsf(EF[i]));
-    mK = fmaxf(mK, fabsf(KF[i]));
+  const int rank = tid & (kMost - 1), part = tid / kMost;  // rows part, part + 8, ... of a column each
+  const int rc = min(rank, R - 1);
+  const bool in = rank < R;
+  // (all loads in flight at once)
+  float v[2][kRowsPer], b[kRowsPer], w[2];
+#pragma unroll
+  for (int j = 0; j < kRowsPer; ++j) {
+    const int i = min(part + kParts * j, kD - 1) * R + rc;
+    v[0][j] = EF[i];
+    v[1][j] = KF[i];
+    b[j] = B[i];
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    mE = fmaxf(mE, __shfl_xor(mE, o));
-    mK = fmaxf(mK, __shfl_xor(mK, o));
-  }
-  if (lane == 0) {
-    red[wave] = mE;
-    red[4 + wave] = mK;
-  }
+  for (int j = 0; j < 2; ++j) w[j] = Wrad[min(part + kParts * j, n_radial - 1) * R + rc];
+  if (part == 0) sG[0][rank] = sG[1][rank] = sCol[0][rank] = sCol[1][rank] = sCol[2][rank] = kNone;
+  if (tid < 3) sTop[tid] = kNone;
+  if (tid < 18) sMax[tid] = 0;
   __syncthreads();
-  const int eE = f16_split_exponent(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
-  const int eK = f16_split_exponent(fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7])));
-  const float sE = ldexpf(1.f, -eE), sK = ldexpf(1.f, -eK);
-  if (blockIdx.x == gridDim.x - 1) {
-    // the largest row norms of the scaled factors, a row per wave; the largest
-    // of 5 |B_r| max_q |Wrad[q, r]| over the ranks
-    float nE = 0.f, nK = 0.f, gb = 0.f;
-    for (int k = wave; k < kD; k += 4) {
-      float e = 0.f, f = 0.f;
-      for (int r = lane; r < R; r += kWave) {
-        const float u = EF[k * R + r] * sE, v = KF[k * R + r] * sK;
-        e += u * u;
-        f += v * v;
+  // exponents of the ranks' columns of B and Wrad, and of KF
+  auto raise = [&](int* p, int e) __attribute__((always_inline)) {
+    if (in && e > kNone / 2) atomicMax(p + rank, e);
+  };
+  int eb = kNone, ek = kNone;
+#pragma unroll
+  for (int j = 0; j < kRowsPer; ++j) {
+    const int k = part + kParts * j;
+    if (k < kD) sF[0][k][rank] = v[0][j], sF[1][k][rank] = v[1][j];
+    eb = max(eb, mag_exp(b[j])), ek = max(ek, mag_exp(v[1][j]));  // (a row past the last is the last)
+  }
+  raise(sG[0], eb);
+  raise(sG[1], max(mag_exp(w[0]), mag_exp(w[1])));
+  raise(sCol[1], ek);
+  __syncthreads();
+  // relative to the largest row; a row that adds nothing stays
+  auto row_exp = [&](int q, int k) __attribute__((always_inline)) {
+    const int e = sRow[q][k];
+    return e == kNone ? 0 : e - sTop[q];
+  };
+  // EF's rows, each rank weighed by what else it multiplies, g and KF's column;
+  // its columns then; and KF's by what EF has not taken
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    if (tid < kD * 32) {
+      const int k = tid / 32;
+      int m = kNone;
+#pragma unroll
+      for (int j = 0; j < kMost / 32; ++j) {
+        const int r = (tid & 31) + 32 * j;
+        const int e = mag_exp(sF[q][k][r]) + sG[0][r] + sG[1][r] + sCol[1 - q][r];
+        if (r < R && e > kNone / 2) m = max(m, e);
       }
 #pragma unroll
-      for (int o = 32; o > 0; o >>= 1) {
-        e += __shfl_xor(e, o);
-        f += __shfl_xor(f, o);
+      for (int o = 16; o > 0; o >>= 1) m = max(m, __shfl_xor(m, o));
+      if ((tid & 31) == 0) {
+        sRow[q][k] = m;
+        atomicMax(&sTop[q], m);
       }
-      nE = fmaxf(nE, e);
-      nK = fmaxf(nK, f);
     }
-    if (tid < R) {
-      float n2 = 0.f, w = 0.f;
-      for (int k = 0; k < kD; ++k) n2 += B[k * R + tid] * B[k * R + tid];
-      for (int q = 0; q < n_radial; ++q) w = fmaxf(w, fabsf(Wrad[q * R + tid]));
-      gb = 5.01f * sqrtf(n2) * w;
-    }
+    __syncthreads();
+    int e = kNone;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) gb = fmaxf(gb, __shfl_xor(gb, o));
+    for (int j = 0; j < kRowsPer; ++j) e = max(e, mag_exp(v[q][j]) - row_exp(q, min(part + kParts * j, kD - 1)));
+    raise(sCol[2 * q], e);
     __syncthreads();
-    if (lane == 0) {
-      red[wave] = nE;
-      red[4 + wave] = nK;
-      red[8 + wave] = gb;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      MatConst c;
-      c.e_fac = eE + eK;
-      int es = 0;
-      (void)frexpf(sqrtf(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]))) *
-                       sqrtf(fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7]))) * 1.01f, &es);
-      c.e_split = es < 14 ? 0 : (es > 60 ? 46 : es - 14);
-      c.g_bound = fmaxf(fmaxf(red[8], red[9]), fmaxf(red[10], red[11]));
-      if (!(c.g_bound > 1e-30f) || !(c.g_bound < 1e30f)) c.g_bound = c.g_bound >= 1e30f ? 1e30f : 1e-30f;
-      *reinterpret_cast<MatConst*>(out + RS * 4096) = c;
+  }
+  // a rank's column scales, if it adds something, and the largest with g's
+  // exponents: |g| times a rank's factor 2^(share - most) is at most 25 * 16
+  const int g_exp = sG[0][rank] + sG[1][rank];
+  int share = sCol[0][rank] + sCol[2][rank], most = share + g_exp;
+  if (most < kNone / 2) share = most = kNone;
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) most = max(most, __shfl_xor(most, o));
+  if (lane == 0 && wave < 2) atomicMax(&sTop[2], most);
+  __syncthreads();
+  most = sTop[2] == kNone ? 0 : sTop[2];
+  auto scaled = [&](int q, int k, int r) __attribute__((always_inline)) {
+    const int e = sCol[2 * q][r];
+    return ldexpf(sF[q][k][r], 14 - row_exp(q, k) - (e == kNone ? 0 : e));
+  };
+  const MatOps O = mat_ops(RS);
+  if (blockIdx.x == 0) {
+    const int s = wave >> 1, l = lane & 31, r0 = 16 * s + 8 * (lane >> 5);
+    if (s >= RS) return;
+    float e[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) e[j] = l < kD && r0 + j < R ? scaled(wave & 1, l, r0 + j) : 0.f;
+    if ((wave & 1) == 0) {
+      float4* eo = reinterpret_cast<float4*>(out) + 2 * s * kWave + lane;
+      eo[0] = make_float4(e[0], e[1], e[2], e[3]);
+      eo[kWave] = make_float4(e[4], e[5], e[6], e[7]);
+    } else {
+      uint32_t u[2][4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) split_f16x2_pair(e[2 * j], e[2 * j + 1], u[0][j], u[1][j]);
+      u32x4* ko = reinterpret_cast<u32x4*>(out + O.off_kf) + 2 * s * kWave + lane;
+      ko[0] = u32x4{u[0][0], u[0][1], u[0][2], u[0][3]};
+      ko[kWave] = u32x4{u[1][0], u[1][1], u[1][2], u[1][3]};
     }
     return;
   }
-  const int s = blockIdx.x * 4 + wave;
-  if (s >= RS) return;
-  const int l = lane & 31, r0 = 16 * s + 8 * (lane >> 5);
-  float e[8];
-  uint32_t w[2][4];
+  // the largest of the scaled factors' row norms (sixteen threads a row) and of
+  // g's bound per radial function; magnitudes compare as integers
+  auto largest = [&](int* p, float m) __attribute__((always_inline)) { atomicMax(p, int(__float_as_uint(m))); };
+  if (tid < 2 * kD * 16) {
+    const int q = tid / (16 * kD), k = tid / 16 - q * kD;
+    float n2 = 0.f;
 #pragma unroll
-  for (int j = 0; j < 8; j += 2) {
-    float k[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const int r = r0 + j + q;
-      const bool ok = l < kD && r < R;
-      e[j + q] = ok ? EF[l * R + r] * sE : 0.f;
-      k[q] = ok ? KF[l * R + r] * sK : 0.f;
+    for (int j = 0; j < kMost / 16; ++j) {
+      const int r = (tid & 15) + 16 * j;
+      const float u = r < R ? scaled(q, k, r) : 0.f;
+      n2 += fabsf(u) <= 16384.f ? u * u : 0.f;
     }
-    split_f16x2_pair(k[0], k[1], w[0][j / 2], w[1][j / 2]);
+#pragma unroll
+    for (int o = 8; o > 0; o >>= 1) n2 += __shfl_xor(n2, o);
+    if ((tid & 15) == 0) largest(&sMax[16 + q], n2);
   }
-  float4* eo = reinterpret_cast<float4*>(out) + 2 * s * kWave + lane;
-  eo[0] = make_float4(e[0], e[1], e[2], e[3]);
-  eo[kWave] = make_float4(e[4], e[5], e[6], e[7]);
-  u32x4* ko = reinterpret_cast<u32x4*>(out + RS * 2048) + 2 * s * kWave + lane;
-  ko[0] = u32x4{w[0][0], w[0][1], w[0][2], w[0][3]};
-  ko[kWave] = u32x4{w[1][0], w[1][1], w[1][2], w[1][3]};
+  {
+    float n2 = 0.f;
+    const int e = sG[0][rank] == kNone ? 0 : -sG[0][rank];
+#pragma unroll
+    for (int j = 0; j < kRowsPer; ++j) {
+      const float u = part + kParts * j < kD ? ldexpf(b[j], e) : 0.f;
+      n2 += fabsf(u) <= 1.f ? u * u : 0.f;
+    }
+    sPart[part][rank] = n2;
+  }
+  __syncthreads();
+  {
+    float n2 = 0.f;
+#pragma unroll
+    for (int p = 0; p < kParts; ++p) n2 += sPart[p][rank];
+    const float n = 5.01f * sqrtf(n2);
+    const int e = sG[1][rank] == kNone ? 0 : -sG[1][rank];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int q = part + kParts * j;
+      const float u = ldexpf(fabsf(w[j]), e);
+      float m = in && q < n_radial && share != kNone && u <= 1.f ? ldexpf(n * u, g_exp + share - most) : 0.f;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
+      if (lane == 0) largest(&sMax[q], m);
+    }
+  }
+  __syncthreads();
+  MatConst* c = reinterpret_cast<MatConst*>(out + O.off_const);
+  if (tid < 16) c->bound[tid] = __uint_as_float(uint32_t(sMax[tid]));
+  if (tid == 0) {
+    c->e_fac = most - 28;
+    int es = 0;
+    (void)frexpf(sqrtf(__uint_as_float(uint32_t(sMax[16]))) * sqrtf(__uint_as_float(uint32_t(sMax[17]))) * 1.01f, &es);
+    c->e_split = es < 14 ? 0 : es - 14;  // (at most 22: 128 ranks below 2^14 each)
+  }
+  if (tid < 16 * RS)
+    reinterpret_cast<float*>(out + O.off_g)[tid] = share == kNone ? 0.f : ldexpf(1.f, min(share - most, 126));
+  if (tid < 2 * kTile) {
+    const int q = tid / kTile, k = tid % kTile;
+    reinterpret_cast<int*>(out + (q ? O.off_rk : O.off_re))[k] = k < kD ? row_exp(q, k) : 0;
+  }
 }
 
 template <bool BF, bool ATT, bool FG>
@@ -161,6 +244,29 @@ bool mat_use(int L, int R, int C, bool bf16, int n_range) {
   return n_range * groups >= mat_detail::kTeams * device_cus();
 }
 
+namespace mat_detail {
+namespace {
+int rank_steps(int R) { return 2 * ((R + kTile - 1) / kTile); }
+}  // namespace
+}  // namespace mat_detail
+
+const int32_t* mat_row_exp(int R, const void* ops) {
+  return reinterpret_cast<const int32_t*>(static_cast<const char*>(ops) +
+                                          mat_detail::mat_ops(mat_detail::rank_steps(R)).off_rk);
+}
+
+hipError_t launch_mat_factor(int R, int n_radial, const float* EF, const float* KF, const float* B,
+                             const float* radial_w, void* ops, hipStream_t s) {
+  using namespace mat_detail;
+  if (R < 1 || R > 128 || n_radial < 1 || n_radial > 16 || !EF || !KF || !B || !radial_w || !ops)
+    return hipErrorInvalidValue;
+  const int RS = rank_steps(R);
+  if (size_t(mat_ops(RS).bytes) > edge_ef_bytes(kD, R)) return hipErrorInvalidValue;
+  k_mat_factor<<<dim3(2), dim3(1024), 0, s>>>(R, RS, n_radial, EF, KF, B, radial_w,
+                                                           static_cast<char*>(ops));
+  return hipGetLastError();
+}
+
 hipError_t launch_cp_edge_mat(const EdgeArgs& a, hipStream_t s) {
   using namespace mat_detail;
   if (a.parts != 1 && a.parts != 2) return hipErrorInvalidValue;
@@ -169,12 +275,7 @@ hipError_t launch_cp_edge_mat(const EdgeArgs& a, hipStream_t s) {
     return hipErrorInvalidValue;
   if (a.fa_global && (a.parts != 2 || a.alpha)) return hipErrorInvalidValue;
   if (a.alpha && (a.parts != 2 || a.n_heads < 1 || a.C % (kTile * a.n_heads) != 0)) return hipErrorInvalidValue;
-  const int RS = 2 * ((a.R + kTile - 1) / kTile);
-  if (size_t(RS) * 4096 + sizeof(MatConst) > edge_ef_bytes(a.d, a.R)) return hipErrorInvalidValue;
-  k_mat_factor<<<dim3((RS + 3) / 4 + 1), dim3(256), 0, s>>>(a.R, RS, a.n_radial, a.EF, a.KF, a.Bf, a.radial_w,
-                                                           static_cast<char*>(a.ef_ops));
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  hipError_t e;
   if (a.parts == 1)
     e = dispatch<true, false, false>(a, s);
   else if (a.fa_global)

@@ -36,14 +36,20 @@
 // each step: harmonics and radial basis at the first, then a 16-rank tile on
 // fp32 MFMA at a time.
 //
-// Scales (exact powers of two, fp32 problems): rows per node, EF and KF per
-// call to [2^13, 2^14); g_e by a bound, |g_e[r]| <= 5 |B_r| max_q |Wrad[q, r]|
-// sum_q phi_q (the harmonics' squares add up to 25) to at most 1, and K_e by
-// max_k |EF_k| max_i |KF_i| to at most 2^14.  2^e undoes an edge's scales, and
-// its product is added in fp32 with that, its row's scale and, in the
-// attention block, its head's weight.  bf16 problems: EF g and KF in one fp16
-// part, K_e rounded to bf16 at its true scale, the sum in the MFMA
-// accumulators.
+// Scales, all exact powers of two.  An fp16 operand holds 28 binary orders at
+// full precision, so what varies between rows, ranks and edges is taken out of
+// it.  EF and KF are scaled per row, by what their ranks can add to K_e there,
+// then per rank (column, to [2^13, 2^14)); a rank's g_e is multiplied by its
+// column scales; and each edge's g is brought below 1 by a bound with a term per
+// radial function q, sum_q phi_q max_r 5 |B_r| |Wrad[q, r]| scale_r (the
+// harmonics' squares add up to 25).  fp32 rounds a rank's g by 2^-24 of its share
+// of that bound; the parts keep 2^-39 of the whole.  K_e is split (fp32 problems)
+// at max_k |EF_k| max_i |KF_i| of the scaled rows.  KF's row scales come back in
+// the feature rows (launch_feature_layout_mat), EF's where a segment's sum is
+// stored, and the others in one exponent per edge: its product is added in fp32
+// with 2^that, its row's scale and, in the attention block, its head's weight.
+// bf16 problems: EF g and KF in one fp16 part, K_e rounded to bf16 with its
+// edge's exponent, the sum in the MFMA accumulators.
 #pragma once
 
 #include <type_traits>
@@ -88,24 +94,25 @@ constexpr int kGeo = 16;    // edges per geometry step
 constexpr int kSub = 2;     // edges per barrier
 
 // LDS of a workgroup, in floats: the matrices [team][2][kSub][2 parts] of
-// [64 lanes] x 16 bytes, the exponents of their products, g
-// [team][2][16][Rp], and per team Y [16][29], Phi [16][17] and, per edge of two
-// geometry steps, the factor of the matrix's split and the exponent.
+// [64 lanes] x 16 bytes, the exponents of their products, the output rows'
+// exponents [32], g [team][2][16][Rp], and per team Y [16][29], Phi [16][17] and
+// the exponent per edge of two geometry steps.
 struct MatSmem {
-  int off_s, off_g, off_team, y, phi, mul, exp, team, floats;
+  int off_s, off_re, off_g, off_team, y, phi, exp, team, floats;
 };
 __host__ __device__ constexpr MatSmem mat_smem(int RS, bool bf) {
   MatSmem s{};
   int o = kTeams * 2 * kSub * (bf ? 2 : 4) * kWave * 4;
   s.off_s = o;
   o += kTeams * 2 * kSub;
+  s.off_re = o;
+  o += kTile;
   s.off_g = o;
   o += kTeams * 2 * kGeo * RS * 16;
   s.off_team = o;
   s.y = 0;
   s.phi = s.y + kGeo * 29;
-  s.mul = s.phi + kGeo * 17;
-  s.exp = s.mul + 2 * kGeo;
+  s.exp = s.phi + kGeo * 17;
   s.team = s.exp + 2 * kGeo;
   s.floats = o + kTeams * s.team;
   return s;
@@ -131,17 +138,29 @@ __device__ __forceinline__ void sh_column(int m, float x, float y, float z, floa
   }
 }
 
-// What the launch's factor kernel leaves in ef_ops, after the operands: the
-// sum of EF's and KF's exponents, the exponent es with |K_e| 2^-(e + e_fac + es)
-// <= 2^14, and the bound of |g| over sum_q phi_q.
-struct MatConst {
-  int e_fac, e_split;
-  float g_bound;
+// What the launch's factor kernel leaves in ef_ops, in bytes: EF's operands,
+// KF's, then MatConst, the ranks' factors of g [16 RS] and the exponents of the
+// output's and the features' rows [32] each, relative to the largest.
+struct MatOps {
+  int off_kf, off_const, off_g, off_re, off_rk, bytes;
 };
-
-__device__ __forceinline__ float pow2(int e) {
-  return __uint_as_float(uint32_t((e < -126 ? -126 : (e > 127 ? 127 : e)) + 127) << 23);
+__host__ __device__ constexpr MatOps mat_ops(int RS) {
+  MatOps o{};
+  o.off_kf = RS * 2048;
+  o.off_const = 2 * o.off_kf;
+  o.off_g = o.off_const + 80;
+  o.off_re = o.off_g + RS * 64;
+  o.off_rk = o.off_re + kTile * 4;
+  o.bytes = o.off_rk + kTile * 4;
+  return o;
 }
+// bound: of |g| times its rank's factor, per radial function; e_fac: a product
+// of the scaled factors and g times 2^e_fac is the true one; e_split: |K_e| of the
+// scaled factors (|g| < 1) is at most 2^(14 + e_split).
+struct MatConst {
+  float bound[16];
+  int e_fac, e_split;
+};
 
 // RS: rank steps of 16.  NT: channel tiles of 32 per applier (the columns of
 // blockIdx.y).  ATT: every edge's message weighted per head (fp32 problems).
@@ -160,7 +179,8 @@ __attribute__((amdgpu_waves_per_eu(kRoles))) void k_cp_edge_mat(EdgeArgs a) {
   const int nr = a.n_radial, R = a.R, C = a.C, E = a.E;
   constexpr MatSmem S = mat_smem(RS, BF);
   u32x4* sK = reinterpret_cast<u32x4*>(smem);
-  int* sS = reinterpret_cast<int*>(smem + S.off_s);  // exponents of the products, or of their segments' sums
+  int* sS = reinterpret_cast<int*>(smem + S.off_s);  // exponents of the products
+  int* sRe = reinterpret_cast<int*>(smem + S.off_re);
   // (the wave's number in a scalar register: everything that follows from it,
   // its range, positions and branches, is uniform)
   const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -178,14 +198,17 @@ __attribute__((amdgpu_waves_per_eu(kRoles))) void k_cp_edge_mat(EdgeArgs a) {
 #pragma unroll
   for (int q = 0; q < kTeams; ++q) most = max(most, bound(b * kTeams + q + 1) - bound(b * kTeams + q));
   const int n_sub = (most + kSub - 1) / kSub;
-  const u32x4* __restrict__ kfp = reinterpret_cast<const u32x4*>(static_cast<const char*>(a.ef_ops) + RS * 2048) + lane;
+  constexpr MatOps O = mat_ops(RS);
+  const char* __restrict__ ops = static_cast<const char*>(a.ef_ops);
+  const u32x4* __restrict__ kfp = reinterpret_cast<const u32x4*>(ops + O.off_kf) + lane;
+  if (threadIdx.x < kTile) sRe[threadIdx.x] = reinterpret_cast<const int*>(ops + O.off_re)[threadIdx.x];
 
   if (role == 0) {
     float* sY = sT + S.y;
     float* sPhi = sT + S.phi;
-    float* sMul = sT + S.mul;
     int* sExp = reinterpret_cast<int*>(sT + S.exp);
-    const MatConst mc = *reinterpret_cast<const MatConst*>(static_cast<const char*>(a.ef_ops) + RS * 4096);
+    const MatConst* __restrict__ mc = reinterpret_cast<const MatConst*>(ops + O.off_const);
+    const float* __restrict__ gm = reinterpret_cast<const float*>(ops + O.off_g);
     // EF, this lane's row k = l32 and ranks 16 s + 8 h + j; KF, row i = l32
     const float4* __restrict__ efp = static_cast<const float4*>(a.ef_ops) + lane;
     float ef[RS * 8];
@@ -211,8 +234,12 @@ __attribute__((amdgpu_waves_per_eu(kRoles))) void k_cp_edge_mat(EdgeArgs a) {
       vy = a.edge_vec[3 * size_t(eid) + 1];
       vz = a.edge_vec[3 * size_t(eid) + 2];
     };
-    // harmonics (the first builder), radial basis and scales (the last one) of
-    // the 16 edges from p on, geometry step number gi
+    float mq[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) mq[q] = mc->bound[gq + 4 * q];
+    const int e_fac = mc->e_fac, e_split = mc->e_split;
+    // harmonics, radial basis and scales of the 16 edges from p on, geometry
+    // step number gi
     auto geometry = [&](int p, int gi) __attribute__((always_inline)) {
       const float len = sqrtf(vx * vx + vy * vy + vz * vz);
       {
@@ -226,26 +253,21 @@ __attribute__((amdgpu_waves_per_eu(kRoles))) void k_cp_edge_mat(EdgeArgs a) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           ph[q] = gq + 4 * q < nr ? radial_phi(len, gq + 4 * q, a.sigma) : 0.f;
-          sum += ph[q];
+          sum += ph[q] * mq[q];
         }
         sum += __shfl_xor(sum, 16);
         sum += __shfl_xor(sum, 32);
         int e = 0;
-        (void)frexpf(mc.g_bound * sum, &e);
-        e = sum < 3.0e38f && sum > 0.f ? (e < -120 ? -120 : (e > 120 ? 120 : e)) : 0;
-        const float sc = pow2(-e);
+        (void)frexpf(sum, &e);
+        e = sum > 0.f && sum < 3.0e38f ? max(e, -120) : 0;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) sPhi[ge * 17 + gq + 4 * q] = ph[q] * sc;
-        const int ex = e + mc.e_fac + mc.e_split;
-        const float mul = BF ? pow2(e + mc.e_fac) : pow2(-mc.e_split);
-        if (gq == 0) {
-          sMul[(gi & 1) * kGeo + ge] = mul;
-          sExp[(gi & 1) * kGeo + ge] = ex;
-        }
+        for (int q = 0; q < 4; ++q) sPhi[ge * 17 + gq + 4 * q] = ldexpf(ph[q], -e);
+        if (gq == 0) sExp[(gi & 1) * kGeo + ge] = e + e_fac + (BF ? 0 : e_split);
       }
       if (p + kGeo < hi) fetch(p + kGeo);
     };
-    // g of 16 edges and the 16 ranks of tile t (rows: edges, columns: ranks)
+    // g, times its ranks' factors, of 16 edges and the 16 ranks of tile t
+    // (rows: edges, columns: ranks)
     auto rank_tile = [&](int t, int gi) __attribute__((always_inline)) {
       const int r = t * 16 + ge, rc = min(r, R - 1);
       const bool ok = r < R;
@@ -272,10 +294,12 @@ __attribute__((amdgpu_waves_per_eu(kRoles))) void k_cp_edge_mat(EdgeArgs a) {
         Tr = mfma16f32(sPhi[ge * 17 + 8 + gq], wo[2], Tr);
         Tr = mfma16f32(sPhi[ge * 17 + 12 + gq], wo[3], Tr);
       }
+      const float m = gm[r];
       float* o = sG + ((gi & 1) * kGeo + 4 * gq) * Rp + t * 16 + ge;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) o[i * Rp] = Ty[i] * Tr[i];
+      for (int i = 0; i < 4; ++i) o[i * Rp] = Ty[i] * (Tr[i] * m);
     };
+    const float split = ldexpf(1.f, -e_split);
     auto build = [&](int i, int gi, int buf, int slot) __attribute__((always_inline)) {
       const float4* gp = reinterpret_cast<const float4*>(sG + ((gi & 1) * kGeo + i) * Rp + 8 * h);
       f32x16 K = f32x16{};
@@ -303,14 +327,15 @@ __attribute__((amdgpu_waves_per_eu(kRoles))) void k_cp_edge_mat(EdgeArgs a) {
         }
         K = mfma_f16(kf[s][0], hi4, K);
       }
-      const float mul = sMul[(gi & 1) * kGeo + i];
+      const int ex = sExp[(gi & 1) * kGeo + i];
+      auto scaled = [&](float v) { return BF ? ldexpf(v, ex) : v * split; };
       u32x4* o = sK + ((team * 2 + buf) * kSub + slot) * (KQ * kWave) + lane;
 #pragma unroll
       for (int q = 0; q < 2; ++q) {
         uint32_t w[2][4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          const float x0 = K[8 * q + 2 * j] * mul, x1 = K[8 * q + 2 * j + 1] * mul;
+          const float x0 = scaled(K[8 * q + 2 * j]), x1 = scaled(K[8 * q + 2 * j + 1]);
           if constexpr (BF)
             w[0][j] = pack_bf16x2_rne(x0, x1);
           else
@@ -320,7 +345,7 @@ __attribute__((amdgpu_waves_per_eu(kRoles))) void k_cp_edge_mat(EdgeArgs a) {
         for (int p = 0; p < P; ++p) o[(p * 2 + q) * kWave] = u32x4{w[p][0], w[p][1], w[p][2], w[p][3]};
       }
       if constexpr (!BF)
-        if (lane == 0) sS[(team * 2 + buf) * kSub + slot] = sExp[(gi & 1) * kGeo + i];
+        if (lane == 0) sS[(team * 2 + buf) * kSub + slot] = ex;
     };
     fetch(lo);
     if (lo < hi) geometry(lo, 0);
@@ -377,7 +402,7 @@ __attribute__((amdgpu_waves_per_eu(kRoles))) void k_cp_edge_mat(EdgeArgs a) {
         float* dl = dst + (4 * h) * C + c;
 #pragma unroll
         for (int v = 0; v < 16; ++v)
-          if (acc_row(v, h) < kD) dl[(8 * (v >> 2) + (v & 3)) * C] = acc[t][v];
+          if (acc_row(v, h) < kD) dl[(8 * (v >> 2) + (v & 3)) * C] = ldexpf(acc[t][v], sRe[acc_row(v, h)]);
       }
       acc[t] = f32x16{};
     });
@@ -421,8 +446,8 @@ __attribute__((amdgpu_waves_per_eu(kRoles))) void k_cp_edge_mat(EdgeArgs a) {
   bool first = true;
   float* part = a.partial + size_t(range) * 2 * dC;
   // The edge at position i of the current 64: its matrix k times its row,
-  // every channel tile's row words replaced by those of the edge NX later once
-  // they are used.
+  // every channel tile's row words replaced by those of the next edge once they
+  // are used.
   auto apply = [&](int i, const u32x4* k, int ex) __attribute__((always_inline)) {
     if ((starts >> i) & 1) {
       if (cur >= 0) {
@@ -441,7 +466,7 @@ __attribute__((amdgpu_waves_per_eu(kRoles))) void k_cp_edge_mat(EdgeArgs a) {
         __builtin_amdgcn_sched_barrier(0);
       });
     } else {
-      const float st = pow2(ex) * __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(scs), i));
+      const float st = ldexpf(__uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(scs), i)), ex);
       f32x16 U[2];
       static_for<NT + 1>([&](auto tc) {
         constexpr int t = decltype(tc)::value;

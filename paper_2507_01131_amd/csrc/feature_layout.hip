@@ -215,11 +215,12 @@ hipError_t launch_packed_pn(int N, int d, int C, const float* x, uint32_t* xp, f
 }
 
 // The same for the L = 4 pass through per-edge matrices
-// (launch_feature_layout_mat): lane (h, c) holds the rows acc_krow(q, h, j),
-// P = 2 fp16 parts with the node's scale, P = 1 bf16.
+// (launch_feature_layout_mat): lane (h, c) holds the rows acc_krow(q, h, j) at
+// their scales, P = 2 fp16 parts with the node's scale, P = 1 bf16.
 template <int MT, int P, typename TI>
-__global__ __launch_bounds__(256) void k_feature_layout_mat(int C, const TI* __restrict__ x, uint32_t* __restrict__ xp,
-                                                            float* __restrict__ row_scale) {
+__global__ __launch_bounds__(256) void k_feature_layout_mat(int C, const TI* __restrict__ x,
+                                                            const int32_t* __restrict__ row_exp,
+                                                            uint32_t* __restrict__ xp, float* __restrict__ row_scale) {
   constexpr int d = 25;
   __shared__ float red[4];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -229,13 +230,20 @@ __global__ __launch_bounds__(256) void k_feature_layout_mat(int C, const TI* __r
   float v[MT][14];
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
-    const int c = (wave + 4 * m) * 32 + l32;
-    const TI* src = x + size_t(node) * d * C + c;
+    const TI* src = x + size_t(node) * d * C + min((wave + 4 * m) * 32 + l32, C - 1);
 #pragma unroll
     for (int r = 0; r < 14; ++r) {
-      const int row = r < 8 ? acc_krow(0, h, r) : acc_krow(1, h, r - 8);
-      v[m][r] = (c < C && row < d) ? to_f32(src[size_t(row) * C]) : 0.f;
+      const int row = acc_krow(r / 8, h, r % 8);
+      v[m][r] = to_f32(src[size_t(min(row, d - 1)) * C]);
     }
+  }
+#pragma unroll
+  for (int r = 0; r < 14; ++r) {
+    const int row0 = acc_krow(r / 8, 0, r % 8), row1 = acc_krow(r / 8, 1, r % 8);
+    const int e = h ? row_exp[row1] : row_exp[row0];
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+      v[m][r] = (wave + 4 * m) * 32 + l32 < C && (h ? row1 : row0) < d ? ldexpf(v[m][r], e) : 0.f;
   }
   float sc = 1.f;
   if constexpr (P == 2) {
@@ -276,11 +284,12 @@ __global__ __launch_bounds__(256) void k_feature_layout_mat(int C, const TI* __r
 }
 
 template <int P, typename TI>
-hipError_t launch_mat_layout(int N, int C, const TI* x, uint32_t* w, float* row_scale, hipStream_t s) {
+hipError_t launch_mat_layout(int N, int C, const TI* x, const int32_t* row_exp, uint32_t* w, float* row_scale,
+                             hipStream_t s) {
   if (C <= 128)
-    k_feature_layout_mat<1, P, TI><<<dim3(N), dim3(256), 0, s>>>(C, x, w, row_scale);
+    k_feature_layout_mat<1, P, TI><<<dim3(N), dim3(256), 0, s>>>(C, x, row_exp, w, row_scale);
   else
-    k_feature_layout_mat<2, P, TI><<<dim3(N), dim3(256), 0, s>>>(C, x, w, row_scale);
+    k_feature_layout_mat<2, P, TI><<<dim3(N), dim3(256), 0, s>>>(C, x, row_exp, w, row_scale);
   return hipGetLastError();
 }
 
@@ -406,17 +415,17 @@ hipError_t launch_feature_layout_packed(int N, int d, int C, const float* x, voi
   }
 }
 
-hipError_t launch_feature_layout_mat(int N, int C, const void* x, bool x_is_f32, int parts, void* xp,
-                                     float* row_scale, hipStream_t s) {
+hipError_t launch_feature_layout_mat(int N, int C, const void* x, bool x_is_f32, int parts, const int32_t* row_exp,
+                                     void* xp, float* row_scale, hipStream_t s) {
   if (N == 0) return hipSuccess;
-  if (!x || !xp || C < 1 || C > 256 || (parts != 1 && parts != 2)) return hipErrorInvalidValue;
+  if (!x || !row_exp || !xp || C < 1 || C > 256 || (parts != 1 && parts != 2)) return hipErrorInvalidValue;
   uint32_t* w = static_cast<uint32_t*>(xp);
   if (parts == 2) {
     if (!x_is_f32 || !row_scale) return hipErrorInvalidValue;
-    return launch_mat_layout<2>(N, C, static_cast<const float*>(x), w, row_scale, s);
+    return launch_mat_layout<2>(N, C, static_cast<const float*>(x), row_exp, w, row_scale, s);
   }
-  return x_is_f32 ? launch_mat_layout<1>(N, C, static_cast<const float*>(x), w, nullptr, s)
-                  : launch_mat_layout<1>(N, C, static_cast<const uint16_t*>(x), w, nullptr, s);
+  return x_is_f32 ? launch_mat_layout<1>(N, C, static_cast<const float*>(x), row_exp, w, nullptr, s)
+                  : launch_mat_layout<1>(N, C, static_cast<const uint16_t*>(x), row_exp, w, nullptr, s);
 }
 
 hipError_t launch_feature_layout(int N, int d, int C, const void* x, bool x_is_f32, int parts, void* xs,

@@ -116,17 +116,22 @@ hipError_t launch_direct_layout(int N, int d, int C, int Cp, const void* x, bool
 // The L = 4 pass through per-edge matrices (cp_edge_mat_impl.hpp): the same
 // result as launch_cp_edge (or, with a.alpha, launch_cp_edge_att) with feat in
 // launch_feature_layout_mat's words; a.pieces_per_block is not used.
-// n_range: the plan's.
+// n_range: the plan's.  launch_mat_factor writes its factors' operands and
+// scales to a.ef_ops, before the layout, which reads the features' row
+// exponents there (mat_row_exp).
 bool mat_use(int L, int R, int C, bool bf16, int n_range);
+hipError_t launch_mat_factor(int R, int n_radial, const float* EF, const float* KF, const float* B,
+                             const float* radial_w, void* ops, hipStream_t s);
+const int32_t* mat_row_exp(int R, const void* ops);
 hipError_t launch_cp_edge_mat(const EdgeArgs& a, hipStream_t s);
 // Its features (d = 25): lane (h, c) of channel tile ct holds the degree rows
 // acc_krow(q, h, j): q = 0, j = 0..7 in four words of fp16 hi parts, then four
 // of lo parts, and q = 1, j = 0..5 in three words each (rows from 26 on do not
 // exist); per node and tile [part][64 lanes][4] words, then [part][64
-// lanes][3].  parts = 1: bf16, one part.  row_scale as
-// launch_feature_layout_packed (parts = 2).
-hipError_t launch_feature_layout_mat(int N, int C, const void* x, bool x_is_f32, int parts, void* xp,
-                                     float* row_scale, hipStream_t s);
+// lanes][3].  Row i is multiplied by 2^row_exp[i] (32 entries).  parts = 1:
+// bf16, one part.  row_scale as launch_feature_layout_packed (parts = 2).
+hipError_t launch_feature_layout_mat(int N, int C, const void* x, bool x_is_f32, int parts, const int32_t* row_exp,
+                                     void* xp, float* row_scale, hipStream_t s);
 // The partial rows of segments that span ranges added in range order onto
 // their output rows, and the zero rows of segments without edges (the last
 // step of every range-split edge pass: a.n_range ranges, a.partial).

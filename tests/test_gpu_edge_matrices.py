@@ -4,8 +4,8 @@ many ranges and nodes without edges among them).  The pass is taken from a
 range per team of the device on, so the graphs have 50 to 70 thousand edges.
 Ranks just past a 32-rank tile and at the last one, channel counts with a part
 tile, two, three, five and eight tiles, two and sixteen radial functions, odd
-range lengths, both feature types, rows over 40 binary orders, forward,
-backward and attention.  The bounds are those of every other parity test: 1e-5
+range lengths, both feature types, rows over 40 binary orders, weights far
+from one common scale, forward, backward and attention.  The bounds are those of every other parity test: 1e-5
 for fp32 problems (the two-part fp16 splits keep 22 bits, the sums are fp32),
 2e-2 for bf16 ones (8 bits, rounded features and matrices)."""
 import numpy as np
@@ -81,6 +81,83 @@ def test_forward_and_backward(case):
     check_rows(gx.cpu().numpy()[nodes], rx[nodes], t, "grad_x")
     check_scaled(gv.cpu().numpy()[sel], rv[sel], grad_vec_scale(w, A, B, D, edges=sel), t, "grad_edge_vec")
     assert np.all(np.isfinite(out)) and bool(torch.isfinite(gx).all())
+
+
+def _ldexp(a, e):
+    return np.ldexp(a, e).astype(np.float32)
+
+
+def _weights(kind, w, f, rng):
+    """Factors and radial weights (f: A, B, D) far from one common scale, the
+    products of what they multiply near it."""
+    A, B, D = f
+    R, k = A.shape[1], np.arange(25)[:, None]
+    if kind == "far":  # the largest radial weights at a distance that no edge has
+        n = np.linalg.norm(w["edge_vec"], axis=1, keepdims=True)
+        w["edge_vec"] = (w["edge_vec"] / n * (3.5 + 2.5 * rng.random(n.shape))).astype(np.float32)
+        w["radial_w"][0] *= 1e5
+    elif kind == "ranks":
+        e = rng.integers(-10, 11, (3, R))
+        A, B, D, w["radial_w"] = _ldexp(A, e[0]), _ldexp(B, e[1]), _ldexp(D, e[2]), _ldexp(w["radial_w"], -e.sum(0))
+    elif kind == "rank0":  # one rank's share of g
+        B, D = B.copy(), D.copy()
+        B[:, 0] *= 2.0 ** 20
+        D[:, 0] *= 2.0 ** -20
+    elif kind in ("small", "large"):  # B's squares below and above what fp32 holds
+        s = {"small": -90, "large": 70}[kind]
+        B, D = _ldexp(B, s), _ldexp(D, -s)
+    elif kind == "rows":
+        D = _ldexp(D, -(k % 5) * 3)
+        A, w["x"] = _ldexp(A, -((k + 2) % 5) * 3), _ldexp(w["x"], ((k + 2) % 5) * 3)
+    elif kind == "blocks":  # two groups of rows that share no rank, one of them with a small g
+        keep = (np.arange(R)[None] < R // 2) == (k < 12)
+        A, D = A * keep, D * keep
+        B = B.copy()
+        B[:, R // 2:] *= 2.0 ** -16
+    return A, B, D
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("kind", ["far", "ranks", "rank0", "small", "large", "rows", "blocks"])
+def test_weights_of_wide_range(kind, dtype):
+    """The bounds per row of output and per degree row of it; a rank's, a row's
+    or an edge's own scale must not show in them."""
+    w, f = _problem(970, 700, 50013, 128, 120, 8, True, dtype)
+    A, B, D = _weights(kind, w, f, np.random.default_rng(5))
+    if dtype == "bf16":
+        w["x_bf16"] = workloads.bf16_round(w["x"])
+    inp = device_inputs(w, A, B, D)
+    res = tdn.forward(inp["x"], inp["edge_vec"], inp["edge_index"], inp["A"], inp["B"], inp["D"], inp["W"],
+                      inp["radial_w"], L=4, r_cut=w["r_cut"], edges_sorted=True)
+    gx, _, _ = tdn.backward(res, _t(w["grad_out"]))
+    torch.cuda.synchronize()
+    args = (w["x"], w["edge_index"], w["edge_vec"], A, B, D, w["W"], w["radial_w"], w["r_cut"], 4)
+    t = tol(w)
+    nodes = _nodes(w["N"], 4)
+    ref = layer.forward_at_nodes(nodes, *args)
+    out = res.out.cpu().numpy()[nodes]
+    assert rel_err(out, ref) < t
+    check_rows(out.reshape(-1, 128), ref.reshape(-1, 128), t, "out")
+    sel = np.nonzero(np.isin(w["edge_index"][0], nodes))[0]
+    rx, _, _ = layer.backward(*args, w["grad_out"], perm=sel)
+    gx = gx.cpu().numpy()[nodes]
+    assert rel_err(gx, rx[nodes]) < t
+    check_rows(gx.reshape(-1, 128), rx[nodes].reshape(-1, 128), t, "grad_x")
+
+
+def test_infinity_stays_in_its_row():
+    w, (A, B, D) = _problem(971, 700, 50013, 64, 100, 8, True, "f32")
+    clean = D.copy()
+    D[3, 5], clean[3] = np.inf, 0.0
+    inp = device_inputs(w, A, B, D)
+    res = tdn.forward(inp["x"], inp["edge_vec"], inp["edge_index"], inp["A"], inp["B"], inp["D"], inp["W"],
+                      inp["radial_w"], L=4, r_cut=w["r_cut"], edges_sorted=True)
+    nodes = _nodes(w["N"], 4)
+    ref = layer.forward_at_nodes(nodes, w["x"], w["edge_index"], w["edge_vec"], A, B, clean, w["W"], w["radial_w"],
+                                 w["r_cut"], 4)
+    out, rest = res.out.cpu().numpy()[nodes], np.arange(25) != 3
+    assert not np.isfinite(out[0, 3]).any()
+    check_rows(out[:, rest], ref[:, rest], tol(w), "out")
 
 
 @pytest.mark.parametrize("N,E,C,R,H", [(1500, 60003, 96, 65, 3), (1500, 50001, 128, 128, 4), (500, 60002, 256, 97, 8)])
