@@ -101,8 +101,14 @@ __attribute__((amdgpu_waves_per_eu(NCT == 8 ? 1 : 2))) void k_bwd_dg_direct(BwdD
   f32x4* sAl = reinterpret_cast<f32x4*>(smem);
   float* sDG = smem + S.off_dg;  // [2][MT][kChunk][Rs]: dg over each k tile
 
-  // the workgroup's segments: those that begin in its share of the edges
-  const int b = xcd_remap(blockIdx.x, gridDim.x);
+  // The workgroup's segments.  One for each, or almost two: every gridDim.x-th,
+  // as a workgroup that takes one more than it has to takes the whole launch with
+  // it (by edges, 50 segments: 205 us against 109; d = 36, C = R = 256, 500 on 256
+  // workgroups: the force call 2220 us against 1920).  Else those that begin in
+  // its share of the edges, which evens out their lengths (310 on 256: 1336 us
+  // against 1379 that way).
+  const int grid = gridDim.x;
+  const bool few = a.n_seg <= grid || (4 * a.n_seg > 7 * grid && a.n_seg <= 2 * grid);
   auto first_at = [&](int p) {  // the first segment with offsets[seg] >= p
     int lo = 0, hi = a.n_seg;
     while (lo < hi) {
@@ -114,9 +120,11 @@ __attribute__((amdgpu_waves_per_eu(NCT == 8 ? 1 : 2))) void k_bwd_dg_direct(BwdD
     }
     return lo;
   };
-  const int seg_lo = first_at(int(int64_t(b) * a.E / gridDim.x));
-  const int seg_hi = first_at(int(int64_t(b + 1) * a.E / gridDim.x));
-  if (seg_lo == seg_hi) return;
+  const int b = xcd_remap(blockIdx.x, grid);
+  const int item_lo = few ? int(blockIdx.x) : first_at(int(int64_t(b) * a.E / grid));
+  const int item_hi = few ? a.n_seg : first_at(int(int64_t(b + 1) * a.E / grid));
+  const int step = few ? grid : 1;
+  if (item_lo >= item_hi) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int h = lane >> 5, l32 = lane & 31;
@@ -149,7 +157,8 @@ __attribute__((amdgpu_waves_per_eu(NCT == 8 ? 1 : 2))) void k_bwd_dg_direct(BwdD
     sAl[t] = v;
   }
 
-  for (int seg = seg_lo; seg < seg_hi; ++seg) {
+  for (int item = item_lo; item < item_hi; item += step) {
+    const int seg = few ? xcd_remap(item, a.n_seg) : item;
     const int e_begin = a.offsets[seg], e_end = a.offsets[seg + 1];
     if (e_begin == e_end) continue;
     // Gz[seg] staged in LDS ([d][C], coalesced float4 loads) in the dg region,

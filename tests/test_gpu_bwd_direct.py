@@ -20,7 +20,9 @@ pytestmark = pytest.mark.gpu
 # L, C, R, N, E, edges into one node, dtype
 CASES = [(5, 32, 17, 40, 31, 0, "f32"), (6, 64, 96, 9, 33, 33, "f32"), (5, 128, 161, 300, 64, 3, "f32"),
          (6, 96, 225, 30, 390, 193, "f32"), (5, 256, 256, 12, 97, 65, "f32"), (6, 48, 160, 20, 161, 129, "bf16"),
-         (5, 128, 224, 25, 700, 0, "bf16")]
+         (5, 128, 224, 25, 700, 0, "bf16"),
+         # one segment too few and enough for workgroups of 256 to take two each by number, and two each
+         (5, 64, 250, 448, 1200, 70, "f32"), (5, 64, 250, 449, 1200, 70, "f32"), (6, 32, 225, 512, 700, 40, "bf16")]
 
 
 @pytest.mark.parametrize("L,C,R,N,E,hub,dtype", CASES)
