@@ -90,6 +90,19 @@ def forward_flops(N, E, d, C, R):
     return edge_kernel_flops(N, E, d, C, R) + N * 2 * d * C * C
 
 
+def edge_products(d, C, R, matrices):
+    """fp16 32x32x16 MFMA products per edge that the edge contraction of an
+    fp32 problem issues: through per-edge matrices three per 16 ranks and six
+    per 32 channels, columns in one or two groups of three or four tiles, each
+    with its matrices; else per 32-channel tile and 32-rank tile the packed
+    K-reduction of the three part products, ceil(3 ceil(d/2) / 8) steps."""
+    ct, rt = (C + 31) // 32, (R + 31) // 32
+    if not matrices:
+        return ct * rt * ((3 * ((d + 1) // 2) + 7) // 8)
+    groups = 2 if ct > 4 else 1
+    return groups * (6 * rt + 6 * (3 if (ct + groups - 1) // groups == 3 else 4))
+
+
 def kernel_source_hash():
     h = hashlib.sha256()
     for f in ("cp_edge_impl.hpp", "cp_edge.hip", "cp_edge_mat_impl.hpp", "cp_edge_mat.hip", "sh_device.hpp",
@@ -419,15 +432,8 @@ def main():
         "forward_tflops": forward_flops(N, E, d, C, R) / (ms_step * 1e-3) / 1e12,
     }
     if not bf16:
-        # fp16 MFMA work issued by the edge contraction, in 32x32x16 products:
-        # through per-edge matrices (degree 4, 97 to 128 ranks, at the size of
-        # a batch) three per 16 ranks and six per 32 channels an edge; else per
-        # edge, 32-channel tile and 32-rank tile the packed K-reduction of the
-        # three part products, ceil(3 ceil(d/2) / 8) steps
-        ct, rt = (C + 31) // 32, (R + 31) // 32
-        matrices = d == 25 and 96 < R <= 128 and C > 32 and E >= 50000
-        products = 6 * rt + 6 * ct if matrices else ct * rt * ((3 * ((d + 1) // 2) + 7) // 8)
-        executed = E * products * 2 * 32 * 32 * 16
+        matrices = kern["edge_factors"][1] > 0  # (the form with a launch of its own for the factors)
+        executed = E * edge_products(d, C, R, matrices) * 2 * 32 * 32 * 16
         # the same algorithmic rate against the fp32 MFMA peak (can pass 1,
         # since the work runs on fp16 MFMA) and against the ceiling of fp32
         # products emulated by three fp16 products (fp16 peak / 3)

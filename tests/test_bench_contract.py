@@ -25,3 +25,18 @@ def test_edge_kernel_flops_closed_form():
     per_edge = 2 * R * d * C + 2 * R * d + 17 * R + R * C
     assert bench.edge_kernel_flops(N, E, d, C, R) == E * per_edge + N * 2 * d * R * C
     assert bench.forward_flops(N, E, d, C, R) == bench.edge_kernel_flops(N, E, d, C, R) + N * 2 * d * C * C
+
+
+def test_products_of_the_edge_contraction():
+    """Per edge, by the form that the library took: the rank form's packed steps
+    per pair of tiles, the matrices' products per rank step and channel tile
+    (two groups of columns above 128 channels)."""
+    import bench
+
+    assert bench.edge_products(25, 128, 128, False) == 4 * 4 * 5
+    assert bench.edge_products(36, 80, 175, False) == 3 * 6 * 7
+    assert bench.edge_products(25, 128, 128, True) == 24 + 24
+    assert bench.edge_products(25, 80, 96, True) == 18 + 18
+    assert bench.edge_products(25, 48, 97, True) == 24 + 24  # a part of four tiles
+    assert bench.edge_products(25, 160, 70, True) == 2 * (18 + 18)
+    assert bench.edge_products(25, 256, 128, True) == 2 * (24 + 24)
