@@ -1,7 +1,8 @@
 """GPU parity of the degree-4 edge pass through per-edge matrices at the edges
 of its tiles, against the oracle on sampled nodes (a hub whose segment spans
 many ranges and nodes without edges among them).  The pass is taken from a
-range per team of the device on, so the graphs have 50 to 70 thousand edges.
+range per team of the device on, so the graphs have 50 to 70 thousand edges; that
+it is taken is checked too.
 Ranks just past a 32-rank tile and at the last one, channel counts with a part
 tile, two, three, five and eight tiles, two and sixteen radial functions, odd
 range lengths, both feature types, rows over 40 binary orders, weights far
@@ -21,6 +22,20 @@ from tests._gpu_helpers import (check_rows, check_scaled, device_inputs, grad_ve
 pytestmark = pytest.mark.gpu
 
 HUB = 7  # (no node from N - 5 on has edges)
+
+
+@pytest.fixture(autouse=True)
+def _form():
+    """Every edge pass of a test went through per-edge matrices (the form with a
+    launch of its own for the factors)."""
+    passes = ("cp_edge_fwd", "cp_edge_fwd_att", "cp_edge_bwd_src")
+    tdn.timer_enable(True)
+    for k in (*passes, "edge_factors"):
+        tdn.timer_read(k, reset=True)
+    yield
+    tdn.timer_enable(False)
+    n = [tdn.timer_read(k, reset=True)[1] for k in (*passes, "edge_factors")]
+    assert n[3] == sum(n[:3]) > 0
 
 
 def _t(a):
