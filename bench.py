@@ -50,7 +50,9 @@ the analogue of the paper's speed-up-against-degree figure (Sec. 4.5).
 with the harmonics read from a precomputed table, and with the contraction
 on the vector ALUs (tdn_ablation_forward), each timed beside the product's
 edge kernel (field "ablations"); --ablation-atomics the segmented sum
-replaced by float atomics.
+replaced by float atomics.  Where the product's edge pass goes through
+per-edge matrices, those that replace a choice of the rank form have no ratio
+to it.
 --attention adds the attention block (tdn_attention_forward: attention
 weights from invariant edge inputs, softmax per destination and head, the
 messages weighted per head inside the edge pass; 4 heads, 32 hidden units)
@@ -101,6 +103,13 @@ def edge_products(d, C, R, matrices):
         return ct * rt * ((3 * ((d + 1) // 2) + 7) // 8)
     groups = 2 if ct > 4 else 1
     return groups * (6 * rt + 6 * (3 if (ct + groups - 1) // groups == 3 else 4))
+
+
+def slowdown(variant_ms, product_ms, same_form=True):
+    """An ablation's edge pass over the product's; None where the product's goes
+    through per-edge matrices and the variant replaces a choice of the rank form,
+    as the ratio would hold the change of form too."""
+    return variant_ms / product_ms if same_form else None
 
 
 def kernel_source_hash():
@@ -527,7 +536,7 @@ def main():
         a_step = ev0.elapsed_time(ev1) / args.steps
         line["ablation_atomics"] = {
             "edge_kernel_ms": a_ms / max(1, a_n), "segmented_edge_kernel_ms": edge_ms,
-            "edge_kernel_slowdown": a_ms / max(1, a_n) / edge_ms,
+            "edge_kernel_slowdown": slowdown(a_ms / max(1, a_n), edge_ms, not kern["edge_factors"][1]),
             "ms_per_step": a_step, "value": E / (a_step * 1e-3)}
     if args.ablations and not bf16:
         # the other hot-path choices, each replaced in turn (tdn_ablation_forward)
@@ -546,7 +555,8 @@ def main():
 
             k_ms, f_ms = time_calls(step_abl, torch, tdn, "cp_edge_fwd_ablation", args.steps)
             entry = {"edge_kernel_ms": k_ms, "ms_per_step": f_ms, "value": E / (f_ms * 1e-3),
-                     "edge_kernel_slowdown": k_ms / edge_ms}
+                     "edge_kernel_slowdown": slowdown(k_ms, edge_ms, code == tdn.ABL_FACTORS_GLOBAL or
+                                                      not kern["edge_factors"][1])}
             if code == tdn.ABL_Y_TABLE:
                 entry["table_kernel_ms"], _ = time_calls(step_abl, torch, tdn, "sh_table", max(1, args.steps // 4))
             abl[name] = entry

@@ -222,7 +222,8 @@ tdn_status tdn_attention_forward(const tdn_problem* p, int32_t n_heads, int32_t 
  * (TDN_ERR_BAD_SHAPE, also for an unknown variant).  Results equal the
  * forward's to fp32 rounding (deterministic).  The workspace is
  * tdn_ablation_workspace_size's (the forward's plus the copies or the table).
- * Not for production use: they exist to be timed against the forward. */
+ * Not for production use: they exist to be timed against the forward (all but
+ * the first only where its edge pass takes the rank form). */
 #define TDN_ABL_FACTORS_GLOBAL 1
 #define TDN_ABL_Y_TABLE 2
 #define TDN_ABL_VALU 3

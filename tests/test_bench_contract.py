@@ -31,8 +31,6 @@ def test_products_of_the_edge_contraction():
     """Per edge, by the form that the library took: the rank form's packed steps
     per pair of tiles, the matrices' products per rank step and channel tile
     (two groups of columns above 128 channels)."""
-    import bench
-
     assert bench.edge_products(25, 128, 128, False) == 4 * 4 * 5
     assert bench.edge_products(36, 80, 175, False) == 3 * 6 * 7
     assert bench.edge_products(25, 128, 128, True) == 24 + 24
@@ -40,3 +38,8 @@ def test_products_of_the_edge_contraction():
     assert bench.edge_products(25, 48, 97, True) == 24 + 24  # a part of four tiles
     assert bench.edge_products(25, 160, 70, True) == 2 * (18 + 18)
     assert bench.edge_products(25, 256, 128, True) == 2 * (24 + 24)
+
+
+def test_no_ratio_between_forms_of_the_edge_pass():
+    assert bench.slowdown(0.6, 0.3) == 2.0
+    assert bench.slowdown(0.6, 0.3, False) is None
