@@ -8,17 +8,16 @@
 //   dg_e[r] = sum_c Gh_t[r, c] (A^T x[s_e])[r, c] = sum_k A[k, r] P_e[k, r],
 //   P_e = x[s_e] Gh_t^T   ([d, R], contraction over the C channels).
 //
-// A workgroup takes the segments that begin in its share of the edges, one
-// after the other; each wave takes one 32-row k tile and a pair of 32-rank
-// tiles, whose Gh^T tiles are formed once a segment (fp32 MFMA, K = d; one
-// tile each by the two waves of a pair, exchanged through LDS); in accumulator
-// layout
-// lane l holds Gh^T[ct*32 + acc_row(v, l/32)][rt*32 + l%32], so registers
-// 8q .. 8q+7 are the B operand of one 32x32x16 step of P_e = x[s_e] Gh^T
-// that contracts channels ct*32 + 16q + 8(i/4) + 4h + i%4 (i = 0..7) in
-// half-wave h.  The x operand comes in that channel order from the xd layout
-// (launch_direct_layout): per edge and channel tile one 16-byte load per
-// k tile, K-step and part, one channel tile ahead.
+// A workgroup takes several segments, one after the other; each wave takes one
+// 32-row k tile and a pair of 32-rank tiles, whose Gh^T tiles are formed once a
+// segment (fp32 MFMA, K = d; one tile each by the two waves of a pair, exchanged
+// through LDS); in accumulator layout lane l holds
+// Gh^T[ct*32 + acc_row(v, l/32)][rt*32 + l%32], so registers 8q .. 8q+7 are the B
+// operand of one 32x32x16 step of P_e = x[s_e] Gh^T that contracts channels
+// ct*32 + 16q + 8(i/4) + 4h + i%4 (i = 0..7) in half-wave h.  The x operand comes
+// in that channel order from the xd layout (launch_direct_layout): per edge and
+// channel tile one 16-byte load per k tile, K-step and part, one or two channel
+// tiles ahead.
 //
 // Arithmetic.  fp32 problems: x[n] 2^-e_n and the wave's Gh^T tiles scaled by
 // a power of two (largest magnitude to [2^13, 2^14)) are split into two fp16
@@ -80,7 +79,6 @@ __device__ __forceinline__ f32x16 mfma16(u32x4 a, u32x4 b, f32x16 c) {
 // Waves of the workgroup: MT k tiles x ceil(RT / 2) pairs of rank tiles.
 __host__ __device__ constexpr int direct_waves(int MT, int RT) { return MT * ((RT + 1) / 2); }
 
-// dg of every edge, by edge id.
 // Whether the two waves of a rank-tile pair form one Gh^T tile each (up to
 // four channel tiles; beyond, the exchange would not fit the LDS), and the
 // floats of the exchange: half a tile and an exponent per wave.
@@ -89,6 +87,7 @@ __host__ __device__ constexpr int gh_floats(int MT, int RT, int NCT, int P) {
   return gh_shared(MT, NCT) ? direct_waves(MT, RT) * (NCT * P * kWave * 4 + 1) : 0;
 }
 
+// dg of every edge, by edge id.
 template <int MT, int RT, int NCT, bool BF>
 __global__ __launch_bounds__(direct_waves(MT, RT)* kWave)
 __attribute__((amdgpu_waves_per_eu(NCT == 8 ? 1 : 2))) void k_bwd_dg_direct(BwdDstArgs a) {

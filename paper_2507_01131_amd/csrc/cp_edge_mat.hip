@@ -7,17 +7,17 @@ namespace mat_detail {
 
 #define TDN_MAT(RS, NT, BF, ATT, FG) \
   extern template hipError_t launch_mat<RS, NT, BF, ATT, FG>(const EdgeArgs&, hipStream_t);
-#define TDN_MAT_RS(RS)               \
+#define TDN_MAT_RS(RS)                \
   TDN_MAT(RS, 3, false, false, false) \
   TDN_MAT(RS, 4, false, false, false) \
   TDN_MAT(RS, 3, false, true, false)  \
   TDN_MAT(RS, 4, false, true, false)  \
   TDN_MAT(RS, 3, false, false, true)  \
   TDN_MAT(RS, 4, false, false, true)  \
-  TDN_MAT(RS, 4, true, false, false)  \
   TDN_MAT(RS, 8, true, false, false)
 TDN_MAT_RS(6)
 TDN_MAT_RS(8)
+TDN_MAT(8, 4, true, false, false)
 #undef TDN_MAT_RS
 #undef TDN_MAT
 
@@ -212,7 +212,7 @@ template <bool BF, bool ATT, bool FG>
 hipError_t dispatch(const EdgeArgs& a, hipStream_t s) {
   const bool r3 = a.R <= 96;
   if constexpr (BF) {
-    if (a.C <= 128) return r3 ? launch_mat<6, 4, true, false>(a, s) : launch_mat<8, 4, true, false>(a, s);
+    if (a.C <= 128) return launch_mat<8, 4, true, false>(a, s);  // (mat_use: more than 96 ranks)
     return r3 ? launch_mat<6, 8, true, false>(a, s) : launch_mat<8, 8, true, false>(a, s);
   } else {
     // three or four tiles per applier, two groups of columns above 128

@@ -3,7 +3,6 @@
 
 #define TDN_MAT(RS, NT) \
   template hipError_t tdn::mat_detail::launch_mat<RS, NT, true, false>(const tdn::EdgeArgs&, hipStream_t);
-TDN_MAT(6, 4)
 TDN_MAT(6, 8)
 TDN_MAT(8, 4)
 TDN_MAT(8, 8)
