@@ -42,14 +42,14 @@
 // then per rank (column, to [2^13, 2^14)); a rank's g_e is multiplied by its
 // column scales; and each edge's g is brought below 1 by a bound with a term per
 // radial function q, sum_q phi_q max_r 5 |B_r| |Wrad[q, r]| scale_r (the
-// harmonics' squares add up to 25).  fp32 rounds a rank's g by 2^-24 of its share
-// of that bound; the parts keep 2^-39 of the whole.  K_e is split (fp32 problems)
-// at max_k |EF_k| max_i |KF_i| of the scaled rows.  KF's row scales come back in
-// the feature rows (launch_feature_layout_mat), EF's where a segment's sum is
-// stored, and the others in one exponent per edge: its product is added in fp32
-// with 2^that, its row's scale and, in the attention block, its head's weight.
-// bf16 problems: EF g and KF in one fp16 part, K_e rounded to bf16 with its
-// edge's exponent, the sum in the MFMA accumulators.
+// harmonics' squares add up to 25), or by its largest value where the bound is
+// far above it.  K_e is split (fp32 problems) at max_k |EF_k| max_i |KF_i| of the
+// scaled rows.  KF's row scales come back in the feature rows
+// (launch_feature_layout_mat), EF's where a segment's sum is stored, and the
+// others in one exponent per edge: its product is added in fp32 with 2^that, its
+// row's scale and, in the attention block, its head's weight.  bf16 problems:
+// EF g and KF in one fp16 part, K_e rounded to bf16 with its edge's exponent, the
+// sum in the MFMA accumulators.
 #pragma once
 
 #include <type_traits>
@@ -238,6 +238,7 @@ __attribute__((amdgpu_waves_per_eu(kRoles))) void k_cp_edge_mat(EdgeArgs a) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) mq[q] = mc->bound[gq + 4 * q];
     const int e_fac = mc->e_fac, e_split = mc->e_split;
+    float top[4];  // the largest |g| that this lane formed for edges 4 gq + i
     // harmonics, radial basis and scales of the 16 edges from p on, geometry
     // step number gi
     auto geometry = [&](int p, int gi) __attribute__((always_inline)) {
@@ -264,40 +265,72 @@ __attribute__((amdgpu_waves_per_eu(kRoles))) void k_cp_edge_mat(EdgeArgs a) {
         for (int q = 0; q < 4; ++q) sPhi[ge * 17 + gq + 4 * q] = ldexpf(ph[q], -e);
         if (gq == 0) sExp[(gi & 1) * kGeo + ge] = e + e_fac + (BF ? 0 : e_split);
       }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) top[i] = 0.f;
       if (p + kGeo < hi) fetch(p + kGeo);
     };
-    // g, times its ranks' factors, of 16 edges and the 16 ranks of tile t
-    // (rows: edges, columns: ranks)
-    auto rank_tile = [&](int t, int gi) __attribute__((always_inline)) {
-      const int r = t * 16 + ge, rc = min(r, R - 1);
-      const bool ok = r < R;
-      float bo[7], wo[4];
+    // g, times its ranks' factors, of 16 edges and the 16 ranks of each tile from
+    // t0 on (rows: edges, columns: ranks)
+    auto rank_tiles = [&](int t0, int n, int gi) __attribute__((always_inline)) {
+      const char* __restrict__ bp = reinterpret_cast<const char*>(a.Bf);
+      const char* __restrict__ wp = reinterpret_cast<const char*>(a.radial_w);
+      uint32_t bk[7], wk[4];  // byte offsets of the lane's rows
 #pragma unroll
-      for (int s = 0; s < 7; ++s) {
-        const int k = 4 * s + gq;
-        bo[s] = a.Bf[min(k, kD - 1) * R + rc];
-        if (s == 6 && k >= kD) bo[s] = 0.f;
-      }
+      for (int s = 0; s < 7; ++s) bk[s] = uint32_t(min(4 * s + gq, kD - 1) * R) * 4;  // (Y is zero from kD on)
 #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int q = 4 * s + gq;
-        wo[s] = a.radial_w[min(q, nr - 1) * R + rc];  // (Phi is zero from n_radial on)
-        if (!ok || q >= nr) wo[s] = 0.f;
-      }
-      f32x4 Ty = f32x4{}, Tr = f32x4{};
+      for (int s = 0; s < 4; ++s) wk[s] = uint32_t(min(4 * s + gq, nr - 1) * R) * 4;  // (Phi from n_radial on)
+#pragma unroll 2
+      for (int t = t0; t < t0 + n; ++t) {
+        const uint32_t r = t * 16 + ge, rc = uint32_t(min(int(r), R - 1)) * 4;
+        float bo[7], wo[4];
 #pragma unroll
-      for (int s = 0; s < 7; ++s) {
-        Ty = mfma16f32(sY[ge * 29 + 4 * s + gq], bo[s], Ty);
-        if (s < 2) Tr = mfma16f32(sPhi[ge * 17 + 4 * s + gq], wo[s], Tr);
-      }
-      if (nr > 8) {
-        Tr = mfma16f32(sPhi[ge * 17 + 8 + gq], wo[2], Tr);
-        Tr = mfma16f32(sPhi[ge * 17 + 12 + gq], wo[3], Tr);
-      }
-      const float m = gm[r];
-      float* o = sG + ((gi & 1) * kGeo + 4 * gq) * Rp + t * 16 + ge;
+        for (int s = 0; s < 7; ++s) bo[s] = *reinterpret_cast<const float*>(bp + (bk[s] + rc));
 #pragma unroll
-      for (int i = 0; i < 4; ++i) o[i * Rp] = Ty[i] * (Tr[i] * m);
+        for (int s = 0; s < 4; ++s) wo[s] = *reinterpret_cast<const float*>(wp + (wk[s] + rc));
+        const float m = gm[r];  // (zero from R on)
+        f32x4 Ty = f32x4{}, Tr = f32x4{};
+#pragma unroll
+        for (int s = 0; s < 7; ++s) {
+          Ty = mfma16f32(sY[ge * 29 + 4 * s + gq], bo[s], Ty);
+          if (s < 2) Tr = mfma16f32(sPhi[ge * 17 + 4 * s + gq], wo[s], Tr);
+        }
+        if (nr > 8) {
+          Tr = mfma16f32(sPhi[ge * 17 + 8 + gq], wo[2], Tr);
+          Tr = mfma16f32(sPhi[ge * 17 + 12 + gq], wo[3], Tr);
+        }
+        float* o = sG + ((gi & 1) * kGeo + 4 * gq) * Rp + r;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const float v = Ty[i] * (Tr[i] * m);
+          top[i] = fmaxf(top[i], fabsf(v));
+          o[i * Rp] = v;
+        }
+      }
+    };
+    // An edge whose g stays below 2^-6 (2^-14 in bf16 problems; harmonics that
+    // vanish, weights that cancel) has it brought to [1/2, 1) by its largest; a
+    // zero or non-finite one stays.  One edge at a time: there are few.
+    auto level = [&](int gi) __attribute__((always_inline)) {
+      unsigned long long low = 0;  // bit 16 gq + i: edge 4 gq + i
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {  // (an edge's 16 lanes are 16 bits of the ballot)
+        const unsigned long long b = __ballot(top[i] >= (BF ? 0x1p-14f : 0x1p-6f));
+        low |= ((b - 0x0001000100010001ull) & ~b & 0x8000800080008000ull) >> (15 - i);
+      }
+      while (low) {
+        const int at = __builtin_ctzll(low), e = (gi & 1) * kGeo + (at >> 4) * 4 + (at & 15);
+        low &= low - 1;
+        float2* gp = reinterpret_cast<float2*>(sG + e * Rp) + min(lane, Rp / 2 - 1);
+        float2 v = *gp;
+        float mx = fmaxf(fabsf(v.x), fabsf(v.y));
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        int x = 0;
+        if (mx > 0.f && mx <= 3.4028234e38f) (void)frexpf(mx, &x);
+        v.x = ldexpf(v.x, -x), v.y = ldexpf(v.y, -x);
+        if (lane < Rp / 2) *gp = v;
+        if (lane == 0) sExp[e] += x;
+      }
     };
     const float split = ldexpf(1.f, -e_split);
     auto build = [&](int i, int gi, int buf, int slot) __attribute__((always_inline)) {
@@ -350,8 +383,10 @@ __attribute__((amdgpu_waves_per_eu(kRoles))) void k_cp_edge_mat(EdgeArgs a) {
     fetch(lo);
     if (lo < hi) geometry(lo, 0);
     lds_barrier();
-    if (lo < hi)
-      for (int t = 0; t < RS; ++t) rank_tile(t, 0);
+    if (lo < hi) {
+      rank_tiles(0, RS, 0);
+      level(0);
+    }
     lds_barrier();
     for (int j = 0; j < n_sub; ++j) {
       const int p = lo + j * kSub, gi = j / kSteps, js = j % kSteps;
@@ -360,9 +395,8 @@ __attribute__((amdgpu_waves_per_eu(kRoles))) void k_cp_edge_mat(EdgeArgs a) {
 #pragma unroll 1
       for (int q = 0; q < kSub; ++q)
         if (p + q < hi) build(js * kSub + q, gi, j & 1, q);
-      if (js >= 1 && js <= kTileSteps && pn < hi)
-#pragma unroll 1
-        for (int q = 0; q < 2; ++q) rank_tile(2 * (js - 1) + q, gi + 1);
+      if (js >= 1 && js <= kTileSteps && pn < hi) rank_tiles(2 * (js - 1), 2, gi + 1);
+      if (js == kTileSteps && pn < hi) level(gi + 1);
       lds_barrier();
     }
     lds_barrier();

@@ -129,11 +129,17 @@ def _weights(kind, w, f, rng):
         A, D = A * keep, D * keep
         B = B.copy()
         B[:, R // 2:] *= 2.0 ** -16
+    elif kind == "axis":  # every edge where the first ranks' harmonic vanishes, the others' g small
+        n = np.linalg.norm(w["edge_vec"], axis=1)
+        w["edge_vec"] = np.stack([0 * n, 0 * n, np.where(np.arange(n.size) % 2, n, -n)], 1).astype(np.float32)
+        B = np.where((k == 3) & (np.arange(R) < R // 2), B, 0) + np.where((k == 0) & (np.arange(R) >= R // 2),
+                                                                         _ldexp(B, -40), 0)
+        B = B.astype(np.float32)
     return A, B, D
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("kind", ["far", "ranks", "rank0", "small", "large", "rows", "blocks"])
+@pytest.mark.parametrize("kind", ["far", "ranks", "rank0", "small", "large", "rows", "blocks", "axis"])
 def test_weights_of_wide_range(kind, dtype):
     """The bounds per row of output and per degree row of it; a rank's, a row's
     or an edge's own scale must not show in them."""
