@@ -543,7 +543,7 @@ tdn_status tdn_ablation_forward(const tdn_problem* p, int32_t variant, const voi
   tdn::EdgeArgs a = edge_args(*p, offsets, perm, src, dst, edge_vec, A, D, B, radial_w, ws + lay.xt, Z, partial);
   // (the table's variant keeps the rank form at every size)
   const bool mat = variant == tdn::kAblFactorsGlobal && use_mat(*p);
-  if (variant != tdn::kAblValu) 
+  if (variant != tdn::kAblValu)
     TDN_HIP(edge_features(*p, x, true, mat, A, D, B, radial_w, partial, ws + lay.xt, stream));
   if (variant == tdn::kAblFactorsGlobal) a.fa_global = ws + lay.total;
   if (variant == tdn::kAblYTable && E > 0) {

@@ -320,15 +320,14 @@ __attribute__((amdgpu_waves_per_eu(kRoles))) void k_cp_edge_mat(EdgeArgs a) {
       while (low) {
         const int at = __builtin_ctzll(low), e = (gi & 1) * kGeo + (at >> 4) * 4 + (at & 15);
         low &= low - 1;
-        float2* gp = reinterpret_cast<float2*>(sG + e * Rp) + min(lane, Rp / 2 - 1);
-        float2 v = *gp;
-        float mx = fmaxf(fabsf(v.x), fabsf(v.y));
+        float* gp = sG + e * Rp + 2 * min(lane, Rp / 2 - 1);
+        const float v0 = gp[0], v1 = gp[1];
+        float mx = fmaxf(fabsf(v0), fabsf(v1));
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
         int x = 0;
         if (mx > 0.f && mx <= 3.4028234e38f) (void)frexpf(mx, &x);
-        v.x = ldexpf(v.x, -x), v.y = ldexpf(v.y, -x);
-        if (lane < Rp / 2) *gp = v;
+        if (lane < Rp / 2) gp[0] = ldexpf(v0, -x), gp[1] = ldexpf(v1, -x);
         if (lane == 0) sExp[e] += x;
       }
     };

@@ -23,7 +23,9 @@ def _inputs(seed, N, E, L, C, R, sort):
                    W=t(w["W"]), radial_w=t(w["radial_w"]))
 
 
-@pytest.mark.parametrize("N,E,L,C,R,sort", [(40, 900, 2, 32, 32, True), (120, 3000, 4, 128, 128, False)])
+# (through per-edge matrices and the two-kernel destination side at d > 32 too)
+@pytest.mark.parametrize("N,E,L,C,R,sort", [(40, 900, 2, 32, 32, True), (120, 3000, 4, 128, 128, False),
+                                            (700, 50001, 4, 128, 128, False), (60, 900, 6, 64, 96, True)])
 def test_forward_and_backward_replays_match_eager(N, E, L, C, R, sort):
     w, inp = _inputs(11 + L, N, E, L, C, R, sort)
     d = (L + 1) ** 2
