@@ -609,7 +609,7 @@ __global__ __launch_bounds__(kWaves* kWave) __attribute__((amdgpu_waves_per_eu(S
             gzv += dy * sJ[t * 3 * d + 3 * k + 2];
           }
           for (int q = sub; q < nr; q += TPE) {
-            const float u = (rn - float(q) * a.sigma) / a.sigma;
+            const float u = radial_t(rn, q, a.sigma);
             const int i = t * nr + q;
             dr += (sDPhi[i] + sDPhi[chunk * nr + i]) * (-u / a.sigma) * sPhi[i];
           }

@@ -235,7 +235,7 @@ __global__ __launch_bounds__(kEdgeWaves* kWave) __attribute__((amdgpu_waves_per_
 #pragma unroll
         for (int x = 0; x < 3; ++x) g[x] += dy * sJ[e * 3 * d + 3 * k + x];
       }
-      if (l16 < nr) dr = sDPhi[e * nr + l16] * (-((rn - float(l16) * a.sigma) / a.sigma) / a.sigma) * sPhi[e * nr + l16];
+      if (l16 < nr) dr = sDPhi[e * nr + l16] * (-radial_t(rn, l16, a.sigma) / a.sigma) * sPhi[e * nr + l16];
 #pragma unroll
       for (int o = 8; o > 0; o >>= 1) {
 #pragma unroll

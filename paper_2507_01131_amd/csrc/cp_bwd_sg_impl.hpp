@@ -382,7 +382,7 @@ __global__ __launch_bounds__(kWaves* kWave) void k_bwd_dst_sg(BwdDstArgs a, int 
       }
       float dr = 0.f;
       for (int q = 0; q < nr; ++q) {
-        const float u = (rn - float(q) * a.sigma) / a.sigma;
+        const float u = radial_t(rn, q, a.sigma);
         dr += sDPhi[t * nr + q] * (-u / a.sigma) * sPhi[t * nr + q];
       }
       const float inv = 1.f / rn;

@@ -172,8 +172,11 @@ __device__ inline void sh_unit_jacobian_column(int L, int m, float x, float y, f
 
 // Gaussian radial basis: phi_q = exp(-(rn - mu_q)^2 / (2 sigma^2)),
 // mu_q = q * sigma, sigma = r_cut / (n - 1); dphi_q/drn = -(rn - mu_q)/sigma^2 phi_q.
+// mu_q is not rounded by itself, whatever the compiler fuses: hoisted out of a
+// loop over edges its rounding alone is 2e-6 of phi_q at (rn - mu_q) = 3.5 sigma.
+__device__ __forceinline__ float radial_t(float rn, int q, float sigma) { return fmaf(-float(q), sigma, rn) / sigma; }
 __device__ __forceinline__ float radial_phi(float rn, int q, float sigma) {
-  const float t = (rn - float(q) * sigma) / sigma;
+  const float t = radial_t(rn, q, sigma);
   return expf(-0.5f * t * t);
 }
 

@@ -44,3 +44,30 @@ def test_edge_and_radial_gradients(L, C, R, N, E, hub, dtype):
     check_scaled(gv.cpu(), rv, grad_vec_scale(w, A, B, D), tol(w), "grad_edge_vec")
     assert rel_err(gr.cpu(), rr) < tol(w)
     check_elementwise(gr.cpu(), rr, tol(w), "grad_radial_w")
+
+
+@pytest.mark.parametrize("L", [5, 6])
+def test_radial_gradient_near_a_centre(L):
+    """The gradient along an edge is dphi times the slope of the radial
+    function, -(r - mu) / sigma^2 phi: near the centre mu = 13 sigma its relative
+    error is that of r - mu, where sigma = 0.4 and r are known to fp32 and mu must
+    not be rounded by itself (2.1e-7 here, 1e-5 of the slope at 0.02 from the
+    centre).  Edges lie along z, where the harmonics add nothing to that
+    component; 5e-6 is left for the sums of dphi."""
+    w = workloads.random_graph(77 + L, n_nodes=20, n_edges=200, L=L, C=32, R=64)
+    rng = np.random.default_rng(L)
+    f = random_factors(L, 64, L)
+    sigma = 6.0 / 15
+    r = (13 * sigma + rng.choice([-1.0, 1.0], 200) * rng.uniform(0.02, 0.03, 200)).astype(np.float32)
+    w["edge_vec"] = np.stack([0 * r, 0 * r, r], 1).astype(np.float32)
+    w["radial_w"] = np.zeros((16, 64), np.float32)
+    w["radial_w"][13] = rng.standard_normal(64)
+    inp = device_inputs(w, *f)
+    res = tdn.forward(inp["x"], inp["edge_vec"], inp["edge_index"], inp["A"], inp["B"], inp["D"], inp["W"],
+                      inp["radial_w"], L=L, r_cut=6.0, edges_sorted=False)
+    _, _, gv = tdn.backward(res, torch.from_numpy(w["grad_out"]).cuda())
+    _, _, rv = layer.backward(w["x"], w["edge_index"], w["edge_vec"], *f, w["W"], w["radial_w"], 6.0, L,
+                              w["grad_out"])
+    err = np.abs(gv.cpu().numpy()[:, 2] - rv[:, 2]) / np.abs(rv[:, 2])
+    known = 13 * abs(float(np.float32(sigma)) - sigma) / np.abs(r.astype(np.float64) - 13 * sigma)
+    assert np.median(err - known) < 5e-6

@@ -166,6 +166,27 @@ def test_weights_of_wide_range(kind, dtype):
     check_rows(gx.reshape(-1, 128), rx[nodes].reshape(-1, 128), t, "grad_x")
 
 
+def test_radial_basis_far_from_its_centre():
+    """One narrow radial function, 3 to 3.5 widths from its centre 13 sigma,
+    sigma = 0.4: rounding the centre to fp32 by itself would be 2e-6 of the
+    function.  Along the axes lengths are exact, and what the function has left is
+    two roundings of (r - mu) / sigma, 3e-7 of it in the norm; the layer adds at
+    most 6.2e-7 (its splits and sums)."""
+    w, f = _problem(972, 700, 50013, 64, 128, 16, True, "f32")
+    rng = np.random.default_rng(6)
+    w["r_cut"] = 6.0
+    vec = np.zeros((w["E"], 3), np.float32)
+    vec[np.arange(w["E"]), rng.integers(0, 3, w["E"])] = 3.8 + 0.2 * rng.random(w["E"])
+    w["edge_vec"] = vec * rng.choice([-1.0, 1.0], (w["E"], 1)).astype(np.float32)
+    w["radial_w"][np.arange(16) != 13] = 0.0
+    inp = device_inputs(w, *f)
+    res = tdn.forward(inp["x"], inp["edge_vec"], inp["edge_index"], inp["A"], inp["B"], inp["D"], inp["W"],
+                      inp["radial_w"], L=4, r_cut=6.0, edges_sorted=True)
+    nodes = _nodes(w["N"], 4)
+    ref = layer.forward_at_nodes(nodes, w["x"], w["edge_index"], w["edge_vec"], *f, w["W"], w["radial_w"], 6.0, 4)
+    assert rel_err(res.out.cpu().numpy()[nodes], ref) < 1e-6
+
+
 def test_infinity_stays_in_its_row():
     w, (A, B, D) = _problem(971, 700, 50013, 64, 100, 8, True, "f32")
     clean = D.copy()
