@@ -118,6 +118,7 @@ __host__ __device__ constexpr MatSmem mat_smem(int RS, bool bf) {
   return s;
 }
 
+__device__ constexpr float kRecip[5] = {1.f, 1.f / 2.f, 1.f / 3.f, 1.f / 4.f, 1.f / 5.f};
 // Order m (and -m) of the harmonics of a unit vector, l = m .. 4.
 __device__ __forceinline__ void sh_column(int m, float x, float y, float z, float* Y) {
   float re = 1.f, im = 0.f, p = 1.f, p_prev = 0.f;
@@ -131,7 +132,9 @@ __device__ __forceinline__ void sh_column(int m, float x, float y, float z, floa
     const float c = kShNorm.v[l][m] * p;
     Y[l * l + l + m] = c * re;
     if (m > 0) Y[l * l + l - m] = c * im;
-    const float pn = (float(2 * l + 1) * z * p - float(l + m) * p_prev) / float(l - m + 1);
+    // t / (l - m + 1), rounded once: the reciprocal's product and its remainder
+    const float t = float(2 * l + 1) * z * p - float(l + m) * p_prev, q = t * kRecip[l - m];
+    const float pn = fmaf(fmaf(-q, float(l - m + 1), t), kRecip[l - m], q);
     p_prev = p;
     p = pn;
   }
